@@ -171,7 +171,7 @@ lbm_status lbm_adjoint_forward(lbm_adjoint* a, const double* d_rho0, const doubl
     Field F = a->field(nullptr, a->ckpt(0));
     dim3 grid((a->p.nx + 63) / 64, a->p.ny);
     auto k = ver == 2 ? k_init<2> : ver == 3 ? k_init<3> : k_init<1>;
-    hipLaunchKernelGGL(k, grid, dim3(64), 0, a->stream, F, d_rho0, d_ux0, d_uy0, d_T0);
+    hipLaunchKernelGGL(k, grid, dim3(64), 0, a->stream, F, nullptr, d_rho0, d_ux0, d_uy0, d_T0);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "k_init launch");
   }

@@ -422,13 +422,13 @@ lbm_status lbm_init(lbm_handle* h, const double* d_rho, const double* d_ux, cons
   Field F = field_of(h, h->cur ^ 1);  // write into the current buffer
   dim3 grid((h->p.nx + 63) / 64, h->p.ny);
   auto k = h->p.eq_version == 2 ? k_init<2> : h->p.eq_version == 3 ? k_init<3> : k_init<1>;
-  hipLaunchKernelGGL(k, grid, dim3(64), 0, h->stream, F, d_rho, d_ux, d_uy, d_T);
+  // every step kernel writes every node of its output buffer, so the other
+  // buffer needs no state; with NEQ walls it gets one all the same (a wall
+  // node is written by its neighbour's update, not its own)
+  hipLaunchKernelGGL(k, grid, dim3(64), 0, h->stream, F, has_walls(&h->p) ? h->f[h->cur ^ 1] : nullptr, d_rho, d_ux,
+                     d_uy, d_T);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "k_init launch");
-  // the other buffer gets the same state so wall nodes are defined in both
-  e = hipMemcpyAsync(h->f[h->cur ^ 1], h->f[h->cur], 16 * h->plane * sizeof(double), hipMemcpyDeviceToDevice,
-                     h->stream);
-  if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync");
   return LBM_OK;
 }
 

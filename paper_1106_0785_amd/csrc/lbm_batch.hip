@@ -63,7 +63,6 @@ struct lbm_batch {
   std::vector<int> tiled;            // 1: advanced tile by tile (TileInst), 0: as a line (LineInst)
   std::vector<LineInst> host_insts;  // indexed by instance (entries of tiled instances unused)
   std::vector<TileInst> host_tinsts;
-  std::vector<int> tindex;           // instance -> index in host_tinsts, or -1
   std::vector<long long> node_off;   // offset of instance i in concatenated field arrays
   long long total_nodes;
   long long arena_doubles;
@@ -89,6 +88,9 @@ struct lbm_batch {
   int max_chunks;
   int* budget;
   int* flag;       // health flag (flag[0]), first of the STATUS_BYTES status words
+  IoInst* io;        // every instance's place, for the one-launch init / moments / get_f
+  int2* io_blocks;   // (instance, piece of IO_NODES nodes), grouped by equilibrium version
+  int io_begin[5];   // entries of version v: [io_begin[v], io_begin[v + 1])
   unsigned long long* ctr;  // chunk ticket counter of the persistent launches
   int* epoch;               // per chunk: the last block a persistent launch has finished
   int persistent;  // line instances: 1 one persistent launch per version, 0 one launch per h steps
@@ -137,9 +139,10 @@ static int batch_tile_rows(const lbm_params* inst, int32_t n) {
 static int tile_variant(const lbm_params& p) { return p.scheme == 1 ? 2 : (has_walls(&p) ? 1 : 0); }
 
 struct Layout {
-  size_t arena_bytes, insts_off, chunks_off, epoch_off, tinsts_off, tiles_off, tiles2_off, budget_off, flag_off,
-      backup_off, total;
+  size_t arena_bytes, insts_off, chunks_off, epoch_off, tinsts_off, tiles_off, tiles2_off, budget_off, io_off,
+      io_blocks_off, flag_off, backup_off, total;
   long long arena_doubles;
+  long long io_blocks;   // pieces of IO_NODES nodes over all instances
   int max_chunks, ntiled, ntiles, ntiles2;  // ntiles, ntiles2: at the smallest tile heights
   int rows;  // default rows per tile of the tiled instances
   std::vector<long long> off;  // arena offset (doubles) of each instance
@@ -147,7 +150,7 @@ struct Layout {
 
 static lbm_status layout_of(const lbm_params* inst, int32_t n, Layout* L) {
   if (!inst || n < 1) return fail(LBM_EINVAL, "need at least one instance");
-  long long dbl = 0, maxc = 0;
+  long long dbl = 0, maxc = 0, iob = 0;
   int ntiled = 0, ntiles = 0, ntiles2 = 0;
   L->off.assign(n, 0);
   for (int i = 0; i < n; ++i) {
@@ -157,6 +160,7 @@ static lbm_status layout_of(const lbm_params* inst, int32_t n, Layout* L) {
   L->rows = batch_tile_rows(inst, n);
   for (int i = 0; i < n; ++i) {
     const lbm_params& p = inst[i];
+    iob += (line_len(p) + IO_NODES - 1) / IO_NODES;
     if (is_line(p)) {
       const long long N = line_len(p);
       dbl = (dbl + 15) / 16 * 16;
@@ -178,6 +182,8 @@ static lbm_status layout_of(const lbm_params* inst, int32_t n, Layout* L) {
       }
     }
   }
+  if (iob > INT_MAX) return fail(LBM_EINVAL, "batch has too many nodes");
+  L->io_blocks = iob;
   L->arena_doubles = dbl;
   L->max_chunks = (int)maxc;
   L->ntiled = ntiled;
@@ -191,7 +197,9 @@ static lbm_status layout_of(const lbm_params* inst, int32_t n, Layout* L) {
   L->tiles_off = L->tinsts_off + align256((size_t)std::max(ntiled, 1) * sizeof(TileInst));
   L->tiles2_off = L->tiles_off + align256((size_t)(ntiles + 72 + 1) * sizeof(int2));
   L->budget_off = L->tiles2_off + align256((size_t)(ntiles2 + 24 + 1) * sizeof(int2));
-  L->flag_off = L->budget_off + align256((size_t)n * sizeof(int));
+  L->io_off = L->budget_off + align256((size_t)n * sizeof(int));
+  L->io_blocks_off = L->io_off + align256((size_t)n * sizeof(IoInst));
+  L->flag_off = L->io_blocks_off + align256((size_t)iob * sizeof(int2));
   L->backup_off = L->flag_off + STATUS_BYTES;
   L->total = L->backup_off + L->arena_bytes;
   return LBM_OK;
@@ -496,6 +504,24 @@ static hipError_t enqueue_steps(lbm_batch* b, int64_t nsteps, int start_cur, int
   return hipSuccess;
 }
 
+// Group of instance i (IoBuffers): 0 lines, 1 tiled with walls or the
+// flux-limited scheme, 2 plain tiled.
+static int io_group(const lbm_batch* b, int i) {
+  if (!b->tiled[i]) return 0;
+  return tile_variant(b->params[i]) == 0 ? 2 : 1;
+}
+
+// The buffers holding each group's current state, and the others.
+static IoBuffers io_buffers(const lbm_batch* b) {
+  const int cur[3] = {b->cur, b->cur2, b->cur3};
+  IoBuffers B;
+  for (int g = 0; g < 3; ++g) {
+    B.cur[g] = b->arena[cur[g]];
+    B.other[g] = b->arena[cur[g] ^ 1];
+  }
+  return B;
+}
+
 static int launches_for(const lbm_batch* b, int64_t nsteps) {
   return (int)((nsteps + b->sched.h - 1) / b->sched.h);
 }
@@ -532,6 +558,8 @@ lbm_status lbm_batch_create(const lbm_params* inst, int32_t n, void* d_workspace
   b->tile_inst = (int2*)(base + L.tiles_off);
   b->tile_inst2 = (int2*)(base + L.tiles2_off);
   b->budget = (int*)(base + L.budget_off);
+  b->io = (IoInst*)(base + L.io_off);
+  b->io_blocks = (int2*)(base + L.io_blocks_off);
   b->flag = (int*)(base + L.flag_off);
   b->ctr = (unsigned long long*)(base + L.flag_off + 128);
   b->persistent = 0;
@@ -572,7 +600,6 @@ lbm_status lbm_batch_create(const lbm_params* inst, int32_t n, void* d_workspace
   b->host_insts.resize(n);
   b->node_off.resize(n);
   b->tiled.assign(n, 0);
-  b->tindex.assign(n, -1);
   long long node = 0;
   for (int i = 0; i < n; ++i) {
     const lbm_params& p = inst[i];
@@ -582,7 +609,6 @@ lbm_status lbm_batch_create(const lbm_params* inst, int32_t n, void* d_workspace
     node += line_len(p);
     if (!is_line(p)) {
       b->tiled[i] = 1;
-      b->tindex[i] = (int)b->host_tinsts.size();
       TileInst T;
       std::memset(&T, 0, sizeof(T));
       T.off = L.off[i];
@@ -604,8 +630,34 @@ lbm_status lbm_batch_create(const lbm_params* inst, int32_t n, void* d_workspace
   }
   b->total_nodes = node;
   std::vector<int> budget(n, INT_MAX);
+  std::vector<IoInst> io(n);
+  std::vector<int2> io_blocks;
+  io_blocks.reserve(L.io_blocks);
+  for (int i = 0; i < n; ++i) {
+    const lbm_params& p = inst[i];
+    IoInst& I = io[i];
+    I.off = L.off[i];
+    I.pitch = b->tiled[i] ? row_pitch(p.nx) : 0;
+    I.plane = b->tiled[i] ? row_pitch(p.nx) * p.ny : b->host_insts[i].stride;
+    I.node = b->node_off[i];
+    I.N = line_len(p);
+    I.nx = p.nx;
+    I.group = io_group(b, i);
+    I.both = b->tiled[i] && has_walls(&p) ? 1 : 0;
+  }
+  b->io_begin[0] = 0;
+  for (int ver = 1; ver <= 3; ++ver) {
+    b->io_begin[ver] = (int)io_blocks.size();
+    for (int i = 0; i < n; ++i)
+      if (inst[i].eq_version == ver)
+        for (long long k = 0; k * IO_NODES < io[i].N; ++k) io_blocks.push_back(int2{i, (int)k});
+  }
+  b->io_begin[4] = (int)io_blocks.size();
   hipError_t e = hipMemcpyAsync(b->insts, b->host_insts.data(), n * sizeof(LineInst), hipMemcpyHostToDevice, b->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(b->budget, budget.data(), n * sizeof(int), hipMemcpyHostToDevice, b->stream);
+  if (e == hipSuccess) e = hipMemcpyAsync(b->io, io.data(), n * sizeof(IoInst), hipMemcpyHostToDevice, b->stream);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(b->io_blocks, io_blocks.data(), io_blocks.size() * sizeof(int2), hipMemcpyHostToDevice, b->stream);
   if (e == hipSuccess) e = hipMemsetAsync(b->flag, 0, STATUS_BYTES, b->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
   if (e != hipSuccess) {
@@ -631,54 +683,21 @@ int64_t lbm_batch_offset(const lbm_batch* b, int32_t i) {
   return i == b->n ? b->total_nodes : b->node_off[i];
 }
 
-// Field view of instance i in arena buffer buf.
-static Field field_of(const lbm_batch* b, int i, int buf) {
-  const lbm_params& p = b->params[i];
-  Field F;
-  F.nx = p.nx;
-  F.ny = p.ny;
-  double* base;
-  if (b->tiled[i]) {
-    const TileInst& T = b->host_tinsts[b->tindex[i]];
-    base = b->arena[buf] + T.off;
-    F.pitch = T.pitch;
-    F.plane = T.plane;
-  } else {
-    const LineInst& I = b->host_insts[i];
-    base = b->arena[buf] + I.off;
-    F.pitch = p.nx;
-    F.plane = I.stride;
-  }
-  F.fin = base;
-  F.fout = base;
-  return F;
-}
-
-// Buffer holding the current state of instance i.
-static int current_buf(const lbm_batch* b, int i) {
-  if (!b->tiled[i]) return b->cur;
-  return tile_variant(b->params[i]) == 0 ? b->cur3 : b->cur2;
-}
-
 lbm_status lbm_batch_init(lbm_batch* b, const double* d_rho, const double* d_ux, const double* d_uy,
                           const double* d_T) {
   if (!b || !d_rho || !d_ux || !d_uy || !d_T) return fail(LBM_EINVAL, "NULL argument");
-  for (int i = 0; i < b->n; ++i) {
-    const lbm_params& p = b->params[i];
-    const long long k = b->node_off[i];
-    for (int buf = 0; buf < 2; ++buf) {
-      Field F = field_of(b, i, buf);
-      F.fin = nullptr;
-      dim3 grid((p.nx + 63) / 64, p.ny);
-      auto kern = p.eq_version == 2 ? k_init<2> : p.eq_version == 3 ? k_init<3> : k_init<1>;
-      hipLaunchKernelGGL(kern, grid, dim3(64), 0, b->stream, F, d_rho + k, d_ux + k, d_uy + k, d_T + k);
-    }
-  }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return hip_fail(e, "k_init launch");
   b->cur = 0;
   b->cur2 = 0;
   b->cur3 = 0;
+  for (int ver = 1; ver <= 3; ++ver) {
+    const int blocks = b->io_begin[ver + 1] - b->io_begin[ver];
+    if (blocks == 0) continue;
+    auto k = ver == 2 ? k_batch_init<2> : ver == 3 ? k_batch_init<3> : k_batch_init<1>;
+    hipLaunchKernelGGL(k, dim3(blocks), dim3(IO_NODES), 0, b->stream, b->io, b->io_blocks + b->io_begin[ver],
+                       io_buffers(b), d_rho, d_ux, d_uy, d_T);
+  }
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return hip_fail(e, "k_batch_init launch");
   return LBM_OK;
 }
 
@@ -743,35 +762,19 @@ lbm_status lbm_batch_step(lbm_batch* b, int64_t nsteps) {
 
 lbm_status lbm_batch_moments(lbm_batch* b, double* d_rho, double* d_ux, double* d_uy, double* d_T, double* d_p) {
   if (!b) return fail(LBM_EINVAL, "batch is NULL");
-  for (int i = 0; i < b->n; ++i) {
-    const lbm_params& p = b->params[i];
-    const long long k = b->node_off[i];
-    Field F = field_of(b, i, current_buf(b, i));
-    F.fout = nullptr;
-    dim3 grid((p.nx + 63) / 64, p.ny);
-    hipLaunchKernelGGL(k_moments<0>, grid, dim3(64), 0, b->stream, F, d_rho ? d_rho + k : nullptr,
-                       d_ux ? d_ux + k : nullptr, d_uy ? d_uy + k : nullptr, d_T ? d_T + k : nullptr,
-                       d_p ? d_p + k : nullptr);
-  }
+  hipLaunchKernelGGL(k_batch_moments<0>, dim3(b->io_begin[4]), dim3(IO_NODES), 0, b->stream, b->io, b->io_blocks,
+                     io_buffers(b), d_rho, d_ux, d_uy, d_T, d_p);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return hip_fail(e, "k_moments launch");
+  if (e != hipSuccess) return hip_fail(e, "k_batch_moments launch");
   return LBM_OK;
 }
 
 lbm_status lbm_batch_get_f(lbm_batch* b, double* d_f) {
   if (!b || !d_f) return fail(LBM_EINVAL, "NULL argument");
-  for (int i = 0; i < b->n; ++i) {
-    const lbm_params& p = b->params[i];
-    const Field F = field_of(b, i, current_buf(b, i));
-    // source rows: 16 planes of ny rows (plane = ny * pitch for tiled
-    // instances, one row of nx = N nodes per plane for lines)
-    const size_t rows = b->tiled[i] ? (size_t)16 * p.ny : 16;
-    const size_t width = b->tiled[i] ? (size_t)p.nx : (size_t)line_len(p);
-    const size_t spitch = b->tiled[i] ? (size_t)F.pitch : (size_t)F.plane;
-    hipError_t e = hipMemcpy2DAsync(d_f + 16 * b->node_off[i], width * sizeof(double), F.fin, spitch * sizeof(double),
-                                    width * sizeof(double), rows, hipMemcpyDeviceToDevice, b->stream);
-    if (e != hipSuccess) return hip_fail(e, "hipMemcpy2DAsync");
-  }
+  hipLaunchKernelGGL(k_batch_get_f<0>, dim3(b->io_begin[4]), dim3(IO_NODES), 0, b->stream, b->io, b->io_blocks,
+                     io_buffers(b), d_f);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return hip_fail(e, "k_batch_get_f launch");
   return LBM_OK;
 }
 

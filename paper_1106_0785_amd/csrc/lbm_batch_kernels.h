@@ -402,4 +402,92 @@ __global__ __launch_bounds__(128, 1) void k_batch_tiles2(const double* __restric
   fused2_tile<VER, 2, true>(F, &I.hot, &I.cold, I.geom2, e.y, flag);
 }
 
+// Where instance i of a batch lies, for the kernels that read or write every
+// instance at once (initial state, output moments, distributions).
+struct IoInst {
+  long long off;          // offset (doubles) of plane 0 in each arena buffer
+  long long pitch, plane; // doubles between rows and between velocity planes
+  long long node;         // first node in concatenated field arrays
+  long long N;            // nodes
+  int nx;
+  int group;              // which of the three buffer parities it follows
+  int both;               // initial state written to both buffers (tiled instances with NEQ walls)
+};
+
+// Arena buffers of the three groups of instances that advance their
+// buffers separately (lines, walled or flux-limited tiles, plain tiles).
+struct IoBuffers {
+  double* cur[3];
+  double* other[3];
+};
+
+constexpr int IO_NODES = 256;  // nodes per workgroup
+
+// Entry b of `blocks` is (instance, IO_NODES-node piece of it). One launch
+// covers the whole batch, where one per instance left the batch bound by
+// launches: 512 lines (656 k nodes) took 1024 launches (2.6 us each) for
+// their initial state and 512 (2.9 us each) for their moments, 3.6 ms beside
+// 3.3 ms for 200 steps; a piece of 256 nodes gives that batch 2 800
+// workgroups. Bound by HBM: 160 and 168 bytes per node.
+__device__ __forceinline__ bool io_node(const IoInst& I, int piece, long long& k, long long& at) {
+  k = (long long)piece * IO_NODES + threadIdx.x;
+  if (k >= I.N) return false;
+  // (a line's planes hold its nodes back to back, whichever axis it lies on)
+  at = I.off + (I.pitch == 0 ? k : (k / I.nx) * I.pitch + k % I.nx);
+  return true;
+}
+
+// One launch per equilibrium version (its own range of `blocks`).
+template <int VER>
+__global__ __launch_bounds__(IO_NODES) void k_batch_init(const IoInst* __restrict__ insts,
+                                                         const int2* __restrict__ blocks, IoBuffers B,
+                                                         const double* __restrict__ rho, const double* __restrict__ ux,
+                                                         const double* __restrict__ uy, const double* __restrict__ T) {
+  const int2 e = blocks[blockIdx.x];
+  const IoInst& I = insts[e.x];
+  long long k, at;
+  if (!io_node(I, e.y, k, at)) return;
+  const long long g = I.node + k;
+  double f[16];
+  equilibrium_f<VER>(rho[g], ux[g], uy[g], T[g], f);
+  double* p = B.cur[I.group] + at;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) p[i * I.plane] = f[i];
+  if (I.both) {
+    p = B.other[I.group] + at;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) p[i * I.plane] = f[i];
+  }
+}
+
+// (template only so that every translation unit gets its own instance)
+template <int U>
+__global__ __launch_bounds__(IO_NODES) void k_batch_moments(const IoInst* __restrict__ insts,
+                                                            const int2* __restrict__ blocks, IoBuffers B, double* rho,
+                                                            double* ux, double* uy, double* T, double* P) {
+  const int2 e = blocks[blockIdx.x];
+  const IoInst& I = insts[e.x];
+  long long k, at;
+  if (!io_node(I, e.y, k, at)) return;
+  double f[16];
+  const double* p = B.cur[I.group] + at;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) f[i] = p[i * I.plane];
+  write_moments(f, I.node + k, rho, ux, uy, T, P);
+}
+
+template <int U>
+__global__ __launch_bounds__(IO_NODES) void k_batch_get_f(const IoInst* __restrict__ insts,
+                                                          const int2* __restrict__ blocks, IoBuffers B,
+                                                          double* __restrict__ out) {
+  const int2 e = blocks[blockIdx.x];
+  const IoInst& I = insts[e.x];
+  long long k, at;
+  if (!io_node(I, e.y, k, at)) return;
+  const double* p = B.cur[I.group] + at;
+  double* q = out + 16 * I.node + k;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) q[i * I.N] = p[i * I.plane];
+}
+
 }  // namespace lbm

@@ -535,18 +535,39 @@ __global__ __launch_bounds__(64 * WAVES) void k_stream_copy(const double* __rest
 // ---------------------------------------------------------------------------
 // Initial state and output moments.
 // ---------------------------------------------------------------------------
+// `also`: a second buffer that gets the same state (NULL: none).
 template <int VER>
-__global__ void k_init(Field F, const double* __restrict__ rho, const double* __restrict__ ux,
-                       const double* __restrict__ uy, const double* __restrict__ T) {
+__global__ void k_init(Field F, double* __restrict__ also, const double* __restrict__ rho,
+                       const double* __restrict__ ux, const double* __restrict__ uy, const double* __restrict__ T) {
   const int x = blockIdx.x * blockDim.x + threadIdx.x;
   const int y = blockIdx.y;
   if (x >= F.nx) return;
   const long long k = (long long)y * F.nx + x;
   double f[16];
   equilibrium_f<VER>(rho[k], ux[k], uy[k], T[k], f);
-  double* p = F.fout + (long long)y * F.pitch + x;
+  const long long at = (long long)y * F.pitch + x;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) p[i * F.plane] = f[i];
+  for (int i = 0; i < 16; ++i) F.fout[at + i * F.plane] = f[i];
+  if (also) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) also[at + i * F.plane] = f[i];
+  }
+}
+
+// rho, u_x, u_y, T and p of a node's distributions into entry k of the
+// output fields (any may be NULL).
+__device__ __forceinline__ void write_moments(const double* f, long long k, double* rho, double* ux, double* uy,
+                                              double* T, double* P) {
+  double m[16];
+  moments_from_f(f, m);
+  const double r = m[0], ir = 1.0 / r;
+  const double u = m[1] * ir, v = m[2] * ir;
+  const double t = m[3] * ir - 0.5 * (u * u + v * v);
+  if (rho) rho[k] = r;
+  if (ux) ux[k] = u;
+  if (uy) uy[k] = v;
+  if (T) T[k] = t;
+  if (P) P[k] = r * t;
 }
 
 // (template only so that every translation unit gets its own instance)
@@ -559,17 +580,7 @@ __global__ void k_moments(Field F, double* rho, double* ux, double* uy, double* 
   double f[16];
 #pragma unroll
   for (int i = 0; i < 16; ++i) f[i] = p[i * F.plane];
-  double m[16];
-  moments_from_f(f, m);
-  const double r = m[0], ir = 1.0 / r;
-  const double u = m[1] * ir, v = m[2] * ir;
-  const double t = m[3] * ir - 0.5 * (u * u + v * v);
-  const long long k = (long long)y * F.nx + x;
-  if (rho) rho[k] = r;
-  if (ux) ux[k] = u;
-  if (uy) uy[k] = v;
-  if (T) T[k] = t;
-  if (P) P[k] = r * t;
+  write_moments(f, (long long)y * F.nx + x, rho, ux, uy, T, P);
 }
 
 }  // namespace lbm
