@@ -157,6 +157,38 @@ __device__ __forceinline__ double wave_max(double v) {
   return v;
 }
 
+// Entry r (0..3, per lane) of a wavefront's four accumulator values.
+__device__ __forceinline__ double pick(const v4d& v, int r) {
+  const double a = (r & 1) ? v[1] : v[0], b = (r & 1) ? v[3] : v[2];
+  return (r & 2) ? b : a;
+}
+
+// v of lane `lane` (wave-uniform), in every lane.
+__device__ __forceinline__ double from_lane(double v, int lane) {
+  const long long b = __double_as_longlong(v);
+  const unsigned lo = __builtin_amdgcn_readlane((int)b, lane), hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+  return __longlong_as_double(((long long)hi << 32) | lo);
+}
+
+// Where the powers of G stop changing but for a factor. Once X^2 = mu X,
+// X^(2^k) = mu^(2^k - 1) X, and the squarings left have a closed form:
+//   log2 |omega| += log2 |mu| (2^-(j-1) - 2^-squarings)   for X at level j - 1.
+// X^2 = mu X is taken to hold when the largest entry of X^2 - mu X has been
+// below RANK_TOL |mu| max|X| at two squarings in a row: the first says that
+// what the other eigenvalues leave in X is below 2^-46, the second has
+// squared that, so all that is left there is the rounding of one product,
+// which every squaring commits and which enters with its level's weight
+// 2^-j: from level CLOSE_FROM on, 64 units of it weigh less than an eighth of
+// the first squaring's own. Powers that stay off rank one (eigenvalues of
+// equal modulus) are squared to the end. Fig. 2 maps: rank one after 13-21 of
+// the 48 squarings at nine points in ten.
+// The largest component of X^(2^k) depends on the phase of mu^(2^k), which
+// the closed form leaves out: at most 2^-(squarings + 1) in log2 |omega|, so
+// only calls of at least CLOSE_SQUARINGS squarings (the default's) use it.
+constexpr double RANK_TOL = 0x1p-46;
+constexpr int CLOSE_SQUARINGS = 48;
+constexpr int CLOSE_FROM = 10;
+
 // |omega|_max by repeated squaring; one wavefront (= one workgroup) per point
 // at a time, grid-stride over all (set, point) pairs.
 //
@@ -183,7 +215,8 @@ __global__ __launch_bounds__(64) void k_stab_radius(const StabCoef* __restrict__
       xi[r] = im;
     }
     double L = 0.0, frac = 1.0;
-    bool zero = false;
+    bool zero = false, close = false;
+    int top = 0, top_lane = 0;  // where X's largest component is: entry (per lane), lane
     for (int j = 0; j <= squarings; ++j) {
       if (j > 0) {
         // X <- X^2 through LDS: write the accumulator layout, read the operand layouts
@@ -204,18 +237,45 @@ __global__ __launch_bounds__(64) void k_stab_radius(const StabCoef* __restrict__
           ai4 = __builtin_amdgcn_mfma_f64_16x16x4f64(aim, bre, ai4, 0, 0, 0);
         }
         __syncthreads();  // every lane has read X before the next write
+        if (squarings >= CLOSE_SQUARINGS && j >= CLOSE_FROM) {
+          // mu = n / o from the largest entry o of X; both sides times |o|^2
+          const double ore = from_lane(pick(xr, top), top_lane), oim = from_lane(pick(xi, top), top_lane);
+          const double nre = from_lane(pick(ar4, top), top_lane), nim = from_lane(pick(ai4, top), top_lane);
+          const double o2 = ore * ore + oim * oim, n2 = nre * nre + nim * nim;
+          const double mr = nre * ore + nim * oim, mi = nim * ore - nre * oim;
+          double d = 0.0;
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            d = fmax(d, fmax(fabs(o2 * ar4[r] - (mr * xr[r] - mi * xi[r])),
+                             fabs(o2 * ai4[r] - (mr * xi[r] + mi * xr[r]))));
+          if (__all(d * d < RANK_TOL * RANK_TOL * n2 * o2)) {
+            if (close) {
+              L += 0.5 * log2(n2 / o2) * (ldexp(1.0, 1 - j) - ldexp(1.0, -squarings));
+              break;
+            }
+            close = true;
+          } else {
+            close = false;
+          }
+        }
         xr = ar4;
         xi = ai4;
       }
       double m = 0.0;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) m = fmax(m, fmax(fabs(xr[r]), fabs(xi[r])));
+      for (int r = 0; r < 4; ++r) {
+        const double a = fmax(fabs(xr[r]), fabs(xi[r]));
+        top = a > m ? r : top;
+        m = fmax(m, a);
+      }
+      const double own = m;
       m = wave_max(m);
       if (!(m > 0.0)) {  // zero matrix (nilpotent G), or NaN
         zero = m == 0.0;
         L = zero ? 0.0 : m;
         break;
       }
+      top_lane = __builtin_amdgcn_readfirstlane(__ffsll((unsigned long long)__ballot(own == m)) - 1);
       const int ex = ilogb(m);
       const double sc = ldexp(1.0, -ex);
 #pragma unroll

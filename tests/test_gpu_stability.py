@@ -229,3 +229,27 @@ def test_radius_matches_oracle_on_shock_tube_states():
             assert r[k].max() <= 1.0 + TOL_R, (lab, r[k].max())
     log("shock-tube states: worst error / bound %.2f" % worst_ratio)
 
+
+
+def test_closed_form_of_the_last_squarings():
+    """From 48 squarings on, powers that have become rank one are finished in
+    closed form; 47 squarings are always carried out. Both share every
+    squaring up to that point (level 11 at the earliest), so they differ by
+    the rounding of later products, 64 units of 2^-53 at most in a matrix with
+    |X| / |lambda| <= 2^24 at weight 2^-10 (64 x 2^-53 x 2^24 x 2^-10 =
+    2^-33), and by the formula's own truncation, 40 x 2^-47 in log2.
+    Random sets, the Fig. 2 cases, and theta = 0, where eigenvalues are equal
+    and nothing may be closed off early."""
+    import torch
+
+    from paper_1106_0785_amd import stability
+
+    p, s = random_sets(11, 40)
+    p2, s2 = fig2_sets((1, 2, 3))
+    th = torch.tensor(_theta(np.random.default_rng(12), 65), device="cuda")
+    full = stability.omega_max(p + p2, s + s2, th, 47).cpu().numpy()
+    for squarings in (0, 48, 60):
+        r = stability.omega_max(p + p2, s + s2, th, squarings).cpu().numpy()
+        worst = float(np.max(np.abs(np.log2(r) - np.log2(full))))
+        log("squarings %d against 47: worst %.2e in log2" % (squarings, worst))
+        assert worst <= 2.0**-33 + 40 * 2.0**-47
