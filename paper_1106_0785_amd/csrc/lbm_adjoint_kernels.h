@@ -91,30 +91,20 @@ LBM_HD void rec_point(const Field& F, const Hot& c, const Cold* __restrict__ col
   const int xn = x + ox, yn = y + oy;
   const Src sx = resolve(xn, F.nx, c.bc[0], c.bc[1], 0);
   const Src sy = resolve(yn, F.ny, c.bc[2], c.bc[3], 2);
-  // side whose ghost this stencil point is (-1: a stored node); periodic
-  // ghosts are stored nodes after wrapping
-  const int side = (xn < 0 || xn >= F.nx) ? sx.side : ((yn < 0 || yn >= F.ny) ? sy.side : -1);
-  const int kind = side >= 0 ? c.bc[side] : BC_PERIODIC;
-  if (kind == BC_DIRICHLET_EQ) {
-    GA = GB = 0.0;
-    velocity_of(cold->ghost[side], ux, uy);
-    return;
-  }
+  // kind of ghost this stencil point is (periodic: a stored node, perhaps
+  // after wrapping) and its side; selects only, as in resolve()
+  const bool xg = xn < 0 || xn >= F.nx;
+  const int kind = xg ? sx.kind : sy.kind, side = xg ? sx.side : sy.side;
+  const bool fixed = kind == BC_DIRICHLET_EQ, mirror = kind == BC_SPECULAR, zero = kind == BC_ZERO_GRADIENT;
   const long long k = (long long)sy.idx * F.pitch + sx.idx;
-  GA = rec[k + REC_GA * F.plane];
-  GB = rec[k + REC_GB * F.plane];
-  ux = rec[k + REC_UX * F.plane];
-  uy = rec[k + REC_UY * F.plane];
-  if (kind == BC_SPECULAR) {
-    GB = -GB;
-    if (side < 2)
-      ux = -ux;
-    else
-      uy = -uy;
-  } else if (kind == BC_ZERO_GRADIENT) {
-    GA = -GA;
-    GB = -GB;
-  }
+  const double ga = rec[k + REC_GA * F.plane], gb = rec[k + REC_GB * F.plane];
+  const double vx = rec[k + REC_UX * F.plane], vy = rec[k + REC_UY * F.plane];
+  const double* gv = cold->gvel[max(side, 0)];
+  const double gx = gv[0], gy = gv[1];
+  GA = fixed ? 0.0 : zero ? -ga : ga;
+  GB = fixed ? 0.0 : (zero || mirror) ? -gb : gb;
+  ux = fixed ? gx : (mirror && side < 2) ? -vx : vx;
+  uy = fixed ? gy : (mirror && side >= 2) ? -vy : vy;
 }
 
 // Where the transposed convection finds lambda at stencil point (x + ox,

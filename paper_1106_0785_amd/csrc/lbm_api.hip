@@ -114,8 +114,10 @@ void make_coef(const lbm_params* p, Hot* c, Cold* cold) {
   }
   for (int sd = 0; sd < 4; ++sd) {
     for (int j = 0; j < 4; ++j) cold->wall[sd][j] = p->wall[sd][j];
-    if (p->bc[sd] == LBM_BC_DIRICHLET_EQ)
+    if (p->bc[sd] == LBM_BC_DIRICHLET_EQ) {
       equilibrium_f(p->eq_version, p->wall[sd][0], p->wall[sd][1], p->wall[sd][2], p->wall[sd][3], cold->ghost[sd]);
+      velocity_of(cold->ghost[sd], cold->gvel[sd][0], cold->gvel[sd][1]);
+    }
     c->bc[sd] = p->bc[sd];
   }
   c->version = p->eq_version;

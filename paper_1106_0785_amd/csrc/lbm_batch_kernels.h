@@ -91,7 +91,7 @@ __device__ __forceinline__ bool line_chunk(const double* __restrict__ A, double*
 #pragma unroll
     for (int i = 0; i < 16; ++i) f[i] = A[off + (long long)i * stride + lo + t];
     moments_from_f(f, m);
-    ir = 1.0 / m[0];
+    ir = recip(m[0]);
 #pragma unroll
     for (int i = 0; i < 16; ++i) buf[0][i][t] = f[i];
     buf[0][16][t] = m[1] * ir;
@@ -136,21 +136,20 @@ __device__ __forceinline__ bool line_chunk(const double* __restrict__ A, double*
         line_ghost(I, c, 1, f, fp);
         velocity_of(fp, uxp, uyp);
       }
-      const double ux0 = buf[P][16][t], uy0 = buf[P][17][t];
       // the step's arithmetic along the line's axis (the other axis's zero
-      // convection terms left out), the collision from the kept moments
-      double df[16], out[16];
+      // terms left out), the collision from the kept moments
+      double out[16];
       if (I.axis == 0) {
-        ok &= collide_from_moments<VER>(c, m, ir, NbrVel{uxp, uyp, uxm, uym, ux0, uy0, ux0, uy0}, df);
+        ok &= collide_from_moments<VER>(c, m, ir, (uxp - uxm) * c.inv2dx, (uyp - uym) * c.inv2dx, out);
         ConvAxis<0, 0>::run(c, f, fp, fm, out);
       } else {
-        ok &= collide_from_moments<VER>(c, m, ir, NbrVel{ux0, uy0, ux0, uy0, uxp, uyp, uxm, uym}, df);
+        ok &= collide_from_moments<VER>(c, m, ir, -((uyp - uym) * c.inv2dy), (uxp - uxm) * c.inv2dy, out);
         ConvAxis<0, 1>::run(c, f, fp, fm, out);
       }
 #pragma unroll
-      for (int i = 0; i < 16; ++i) out[i] = f[i] + (out[i] + df[i]);
+      for (int i = 0; i < 16; ++i) out[i] += f[i];
       moments_from_f(out, m);
-      ir = 1.0 / m[0];
+      ir = recip(m[0]);
 #pragma unroll
       for (int i = 0; i < 16; ++i) buf[Q][i][t] = out[i];
       buf[Q][16][t] = m[1] * ir;
@@ -167,7 +166,7 @@ __device__ __forceinline__ bool line_chunk(const double* __restrict__ A, double*
         // its velocity as any node's (from its moments), so that it does not
         // depend on whether the next step reloads the node
         moments_from_f(fw, m);
-        ir = 1.0 / m[0];
+        ir = recip(m[0]);
 #pragma unroll
         for (int i = 0; i < 16; ++i) buf[Q][i][t] = fw[i];
         buf[Q][16][t] = m[1] * ir;

@@ -38,6 +38,7 @@ __host__ __device__ __forceinline__ Dual& operator+=(Dual& a, Dual b) {
   a = a + b;
   return a;
 }
+__host__ __device__ __forceinline__ Dual mad(Dual a, Dual b, Dual c) { return a * b + c; }
 __host__ __device__ __forceinline__ Dual sexp(Dual a) {
   const double e = ::exp(a.v);
   return Dual(e, e * a.d);

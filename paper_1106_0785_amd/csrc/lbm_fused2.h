@@ -153,7 +153,7 @@ __device__ __forceinline__ void fused2_tile(Field F, const Hot* __restrict__ hot
     ring0[slot][17][lane + 1] = uy;
     ring0[slot][ep][ecol] = ev;
     const double er = row16_sum(ev), ejx = row16_sum(evx * ev), ejy = row16_sum(evy * ev);
-    const double ir = 1.0 / er;
+    const double ir = recip(er);
     ring0[slot][16][ecol] = ejx * ir;
     ring0[slot][17][ecol] = ejy * ir;
   };
@@ -199,11 +199,10 @@ __device__ __forceinline__ void fused2_tile(Field F, const Hot* __restrict__ hot
     nv.uy_yp = ring0[sp][17][lane + 1];
     nv.ux_ym = ring0[sm][16][lane + 1];
     nv.uy_ym = ring0[sm][17][lane + 1];
-    double df[16];
-    const bool good = collide_delta<VER>(c, f, nv, df);
+    const bool good = collide_delta<VER>(c, f, nv, out);
     ConvLds<0, C0>::run(c, ring0[s0], ring0[sp], ring0[sm], lane + 1, lane + 2, lane, out);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) out[i] = f[i] + (out[i] + df[i]);
+    for (int i = 0; i < 16; ++i) out[i] += f[i];
     ok &= good || X < 0 || X >= nx || rs < 0 || rs >= ny;
     velocity_of(out, ux, uy);
   };
@@ -282,11 +281,11 @@ __device__ __forceinline__ void fused2_tile(Field F, const Hot* __restrict__ hot
       nv.uy_yp = ring1[tp][17][lane];
       nv.ux_ym = ring1[tm][16][lane];
       nv.uy_ym = ring1[tm][17][lane];
-      double df[16], out[16];
-      const bool good = collide_delta<VER>(c, f, nv, df);
+      double out[16];
+      const bool good = collide_delta<VER>(c, f, nv, out);
       ConvLds<0, C1>::run(c, ring1[t0], ring1[tp], ring1[tm], lane, cr, cl, out);
 #pragma unroll
-      for (int k = 0; k < 16; ++k) out[k] = f[k] + (out[k] + df[k]);
+      for (int k = 0; k < 16; ++k) out[k] += f[k];
       const bool store = lane >= 1 && lane <= OSTRIP && X < nx;
       ok &= good || !store;
       if (store) {

@@ -24,31 +24,35 @@ struct Src {
   int idx;
   int mode;
   int side;
+  int kind = BC_PERIODIC;  // boundary kind of the side a ghost lies beyond (a stored node, or a wrap: periodic)
 };
 
 // Ghost layers are up to two deep (radius-2 scheme): a periodic ghost wraps,
 // a zero-gradient ghost repeats the boundary node, a mirror ghost takes the
 // mirror image about the wall half a spacing outside the boundary node
 // (-1 -> 0, -2 -> 1), a fixed-state ghost is that state's equilibrium.
+// i is at most two past either end (-2 .. n + 1), so a wrap is at most two
+// periods (n = 1). Written with selects only: the branches of a switch here
+// diverge between lanes, and values that the register allocator moved at
+// their end were moved under the branch's lane mask.
 LBM_HD Src resolve(int i, int n, int bc_lo, int bc_hi, int side_lo) {
-  Src s{i, 0, -1};
-  if (i < 0) {
-    s.side = side_lo;
-    switch (bc_lo) {
-      case BC_PERIODIC: s.idx = ((i % n) + n) % n; break;
-      case BC_SPECULAR: s.idx = min(-1 - i, n - 1); s.mode = 1; break;
-      case BC_DIRICHLET_EQ: s.idx = 0; s.mode = 2; break;
-      default: s.idx = 0; break;  // zero-gradient; a NEQ-wall side's ghost is never used
-    }
-  } else if (i >= n) {
-    s.side = side_lo + 1;
-    switch (bc_hi) {
-      case BC_PERIODIC: s.idx = i % n; break;
-      case BC_SPECULAR: s.idx = max(2 * n - 1 - i, 0); s.mode = 1; break;
-      case BC_DIRICHLET_EQ: s.idx = n - 1; s.mode = 2; break;
-      default: s.idx = n - 1; break;
-    }
-  }
+#if defined(__HIP_DEVICE_COMPILE__)
+  // (one problem per workgroup: the codes are wave-uniform)
+  bc_lo = __builtin_amdgcn_readfirstlane(bc_lo);
+  bc_hi = __builtin_amdgcn_readfirstlane(bc_hi);
+#endif
+  const bool lo = i < 0, hi = i >= n, out = lo | hi;
+  const int bc = lo ? bc_lo : bc_hi;
+  int wrap = lo ? i + n : i - n;
+  wrap += wrap < 0 ? n : 0;
+  wrap -= wrap >= n ? n : 0;
+  const int mirror = lo ? min(-1 - i, n - 1) : max(2 * n - 1 - i, 0);
+  const int edge = lo ? 0 : n - 1;  // zero-gradient, fixed state; a NEQ-wall side's ghost is never used
+  Src s;
+  s.idx = !out ? i : bc == BC_PERIODIC ? wrap : bc == BC_SPECULAR ? mirror : edge;
+  s.mode = out && bc == BC_SPECULAR ? 1 : out && bc == BC_DIRICHLET_EQ ? 2 : 0;
+  s.side = lo ? side_lo : hi ? side_lo + 1 : -1;
+  s.kind = out ? bc : (int)BC_PERIODIC;
   return s;
 }
 
@@ -188,10 +192,11 @@ __global__ __launch_bounds__(256) void k_step_plain(Field F, const Hot* __restri
     load_point(F, cold, resolve(x - 2, F.nx, c.bc[0], c.bc[1], 0), cy, fxm2);
     load_point(F, cold, cx, resolve(y + 2, F.ny, c.bc[2], c.bc[3], 2), fyp2);
     load_point(F, cold, cx, resolve(y - 2, F.ny, c.bc[2], c.bc[3], 2), fym2);
+    ok = collide_delta<VER>(c, f, nv, out);
 #pragma unroll
     for (int i = 0; i < 16; ++i)
-      out[i] = convect_limited_i(c, i, f[i], fxm2[i], fxm[i], fxp[i], fxp2[i], fym2[i], fym[i], fyp[i], fyp2[i]);
-    ok = collide_add<VER>(c, f, nv, out);
+      out[i] = f[i] + (out[i] + convect_limited_i(c, i, f[i], fxm2[i], fxm[i], fxp[i], fxp2[i], fym2[i], fym[i],
+                                                  fyp[i], fyp2[i]));
   } else {
     ok = node_update<VER>(c, f, fxp, fxm, fyp, fym, nv, out);
   }
@@ -219,14 +224,14 @@ constexpr int STRIP = 64;
 constexpr int WAVES = 4;  // wavefronts per workgroup of the default tile shape
 constexpr int NV = 18;    // 16 distributions + u_x + u_y per ring entry
 
-// Convection of all 16 velocities with the stencil values read from the LDS
+// Adds the convection of all 16 velocities to out, with the stencil values read from the LDS
 // ring rows (current row r0, rows above/below rp/rm) as they are needed; c0,
 // cp, cm are the ring columns of the node and its x+1 / x-1 neighbours.
 template <int I, int RWT>
 struct ConvLds {
   __device__ __forceinline__ static void run(const Hot& c, const double (*r0)[RWT], const double (*rp)[RWT],
                                              const double (*rm)[RWT], int c0, int cp, int cm, double* out) {
-    out[I] = convect<I>(c, r0[I][c0], VX[I] ? r0[I][cp] : 0.0, VX[I] ? r0[I][cm] : 0.0,
+    out[I] = convect<I>(c, out[I], r0[I][c0], VX[I] ? r0[I][cp] : 0.0, VX[I] ? r0[I][cm] : 0.0,
                         VY[I] ? rp[I][c0] : 0.0, VY[I] ? rm[I][c0] : 0.0);
     ConvLds<I + 1, RWT>::run(c, r0, rp, rm, c0, cp, cm, out);
   }
@@ -244,7 +249,7 @@ struct ConvLim {
   __device__ __forceinline__ static void run(const Hot& c, const double (*r2m)[RWT], const double (*r1m)[RWT],
                                              const double (*r0)[RWT], const double (*r1p)[RWT],
                                              const double (*r2p)[RWT], int c0, double* out) {
-    out[I] = convect_limited<I>(c, r0[I][c0], VX[I] ? r0[I][c0 - 2] : 0.0, VX[I] ? r0[I][c0 - 1] : 0.0,
+    out[I] += convect_limited<I>(c, r0[I][c0], VX[I] ? r0[I][c0 - 2] : 0.0, VX[I] ? r0[I][c0 - 1] : 0.0,
                                 VX[I] ? r0[I][c0 + 1] : 0.0, VX[I] ? r0[I][c0 + 2] : 0.0,
                                 VY[I] ? r2m[I][c0] : 0.0, VY[I] ? r1m[I][c0] : 0.0, VY[I] ? r1p[I][c0] : 0.0,
                                 VY[I] ? r2p[I][c0] : 0.0);
@@ -376,7 +381,7 @@ __device__ __forceinline__ void fused_tile(Field F, const Hot* __restrict__ hot,
     // neighbour columns: every lane of a DPP row writes the same values
     ring[slot][ep][ecol] = ev;
     const double er = row16_sum(ev), ejx = row16_sum(evx * ev), ejy = row16_sum(evy * ev);
-    const double ir = 1.0 / er;
+    const double ir = recip(er);
     ring[slot][16][ecol] = ejx * ir;
     ring[slot][17][ecol] = ejy * ir;
   };
@@ -434,15 +439,7 @@ __device__ __forceinline__ void fused_tile(Field F, const Hot* __restrict__ hot,
     if (FULL || y < y1) {
       if (!WALLS || !is_wall_node(c, x, y, F.nx, F.ny)) {
         const int s0 = (y - base) % RING, sp = (y + 1 - base) % RING, sm = (y - 1 - base) % RING;
-        double out[16];
-        // convection first, reading each neighbour value from LDS as it is used
-        if constexpr (HR == 1) {
-          ConvLds<0, RWT>::run(c, ring[s0], ring[sp], ring[sm], c0, c0 + 1, c0 - 1, out);
-        } else {
-          const int sp2 = (y + 2 - base) % RING, sm2 = (y - 2 - base) % RING;
-          ConvLim<0, RWT>::run(c, ring[sm2], ring[sm], ring[s0], ring[sp], ring[sp2], c0, out);
-        }
-        double f[16];
+        double f[16], out[16];
 #pragma unroll
         for (int i = 0; i < 16; ++i) f[i] = ring[s0][i][c0];
         NbrVel nv;
@@ -454,7 +451,16 @@ __device__ __forceinline__ void fused_tile(Field F, const Hot* __restrict__ hot,
         nv.uy_yp = ring[sp][17][c0];
         nv.ux_ym = ring[sm][16][c0];
         nv.uy_ym = ring[sm][17][c0];
-        ok &= collide_add<VER>(c, f, nv, out) || x >= F.nx;
+        ok &= collide_delta<VER>(c, f, nv, out) || x >= F.nx;
+        // the convection reads each neighbour value from LDS as it is used
+        if constexpr (HR == 1) {
+          ConvLds<0, RWT>::run(c, ring[s0], ring[sp], ring[sm], c0, c0 + 1, c0 - 1, out);
+        } else {
+          const int sp2 = (y + 2 - base) % RING, sm2 = (y - 2 - base) % RING;
+          ConvLim<0, RWT>::run(c, ring[sm2], ring[sm], ring[s0], ring[sp], ring[sp2], c0, out);
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) out[i] += f[i];
         if constexpr (NT)
           store_node_stream(F, x, y, out);
         else

@@ -33,6 +33,7 @@ struct Hot {
 struct Cold {
   double ghost[4][16];  // equilibrium ghosts of DIRICHLET_EQ sides
   double wall[4][4];    // (rho, ux, uy, T) per side for NEQ walls
+  double gvel[4][2];    // velocities of the ghosts
 };
 
 // Neighbour velocities the modification needs.
@@ -44,28 +45,29 @@ struct NbrVel {
 LBM_HD void velocity_of(const double* f, double& ux, double& uy) {
   double rho, jx, jy;
   density_momentum(f, rho, jx, jy);
-  const double ir = 1.0 / rho;
+  const double ir = recip(rho);
   ux = jx * ir;
   uy = jy * ir;
 }
 
-// Lax-Wendroff convection increment of velocity I (Sec. III, G_ij):
-// sum over axes of p (f(+1) - f) + m (f(-1) - f), with p = (c^2 - c)/2 and
-// m = (c^2 + c)/2 for c = v dt/dx. Written with differences so that a
+// Adds to v the Lax-Wendroff convection increment of velocity I (Sec. III,
+// G_ij): sum over axes of p (f(+1) - f) + m (f(-1) - f), with p = (c^2 - c)/2
+// and m = (c^2 + c)/2 for c = v dt/dx. Written with differences so that a
 // uniform state is reproduced exactly and the grid totals of rho, j, e are
 // conserved to rounding (a centre coefficient 1 - c^2 would scale every
-// distribution by a rounding bias each step).
+// distribution by a rounding bias each step). Starting from the collision's
+// increment leaves two differences and two fused multiply-adds per axis.
 template <int I>
-LBM_HD double convect(const Hot& c, double f, double fxp, double fxm, double fyp, double fym) {
-  double v = 0.0;
-  if (VX[I] == 1) v += c.lx[0] * (fxp - f) + c.lx[1] * (fxm - f);
-  if (VX[I] == -1) v += c.lx[1] * (fxp - f) + c.lx[0] * (fxm - f);
-  if (VX[I] == 2) v += c.lx[2] * (fxp - f) + c.lx[3] * (fxm - f);
-  if (VX[I] == -2) v += c.lx[3] * (fxp - f) + c.lx[2] * (fxm - f);
-  if (VY[I] == 1) v += c.ly[0] * (fyp - f) + c.ly[1] * (fym - f);
-  if (VY[I] == -1) v += c.ly[1] * (fyp - f) + c.ly[0] * (fym - f);
-  if (VY[I] == 2) v += c.ly[2] * (fyp - f) + c.ly[3] * (fym - f);
-  if (VY[I] == -2) v += c.ly[3] * (fyp - f) + c.ly[2] * (fym - f);
+LBM_HD double convect(const Hot& c, double v, double f, double fxp, double fxm, double fyp, double fym) {
+  constexpr int ax = VX[I] < 0 ? -VX[I] : VX[I], ay = VY[I] < 0 ? -VY[I] : VY[I];
+  if constexpr (ax != 0) {
+    v = mad(c.lx[2 * (ax - 1) + (VX[I] > 0 ? 0 : 1)], fxp - f, v);
+    v = mad(c.lx[2 * (ax - 1) + (VX[I] > 0 ? 1 : 0)], fxm - f, v);
+  }
+  if constexpr (ay != 0) {
+    v = mad(c.ly[2 * (ay - 1) + (VY[I] > 0 ? 0 : 1)], fyp - f, v);
+    v = mad(c.ly[2 * (ay - 1) + (VY[I] > 0 ? 1 : 0)], fym - f, v);
+  }
   return v;
 }
 
@@ -116,9 +118,9 @@ LBM_HD double convect_limited_i(const Hot& c, int i, double f, double x2m, doubl
 template <int I>
 struct ConvAll {
   LBM_HD static void run(const Hot& c, const double* f, const double* fxp, const double* fxm, const double* fyp,
-                         const double* fym, double* out) {
-    out[I] = convect<I>(c, f[I], fxp[I], fxm[I], fyp[I], fym[I]);
-    ConvAll<I + 1>::run(c, f, fxp, fxm, fyp, fym, out);
+                         const double* fym, double* acc) {
+    acc[I] = convect<I>(c, acc[I], f[I], fxp[I], fxm[I], fyp[I], fym[I]);
+    ConvAll<I + 1>::run(c, f, fxp, fxm, fyp, fym, acc);
   }
 };
 template <>
@@ -127,25 +129,25 @@ struct ConvAll<16> {
                          double*) {}
 };
 
-// The Lax-Wendroff increment of velocity I along one axis only (AXIS 0: x,
-// 1: y), for a node whose neighbours along the other axis are itself (a
-// one-dimensional problem: those terms are exact zeros, left out).
+// The same along one axis only (AXIS 0: x, 1: y), for a node whose
+// neighbours along the other axis are itself (a one-dimensional problem:
+// those terms are exact zeros, left out).
 template <int I, int AXIS>
-LBM_HD double convect_axis(const Hot& c, double f, double fp, double fm) {
-  constexpr int v = AXIS == 0 ? VX[I] : VY[I];
+LBM_HD double convect_axis(const Hot& c, double v, double f, double fp, double fm) {
+  constexpr int vel = AXIS == 0 ? VX[I] : VY[I], k = vel < 0 ? -vel : vel;
   const double* l = AXIS == 0 ? c.lx : c.ly;
-  if (v == 1) return l[0] * (fp - f) + l[1] * (fm - f);
-  if (v == -1) return l[1] * (fp - f) + l[0] * (fm - f);
-  if (v == 2) return l[2] * (fp - f) + l[3] * (fm - f);
-  if (v == -2) return l[3] * (fp - f) + l[2] * (fm - f);
-  return 0.0;
+  if constexpr (k != 0) {
+    v = mad(l[2 * (k - 1) + (vel > 0 ? 0 : 1)], fp - f, v);
+    v = mad(l[2 * (k - 1) + (vel > 0 ? 1 : 0)], fm - f, v);
+  }
+  return v;
 }
 
 template <int I, int AXIS>
 struct ConvAxis {
-  LBM_HD static void run(const Hot& c, const double* f, const double* fp, const double* fm, double* out) {
-    out[I] = convect_axis<I, AXIS>(c, f[I], fp[I], fm[I]);
-    ConvAxis<I + 1, AXIS>::run(c, f, fp, fm, out);
+  LBM_HD static void run(const Hot& c, const double* f, const double* fp, const double* fm, double* acc) {
+    acc[I] = convect_axis<I, AXIS>(c, acc[I], f[I], fp[I], fm[I]);
+    ConvAxis<I + 1, AXIS>::run(c, f, fp, fm, acc);
   }
 };
 template <int AXIS>
@@ -154,56 +156,48 @@ struct ConvAxis<16, AXIS> {
 };
 
 // Collision of one node in velocity space, -dt M^-1 Q (Sec. II), into df,
-// from the node's moments m = M f and ir = 1 / m[0]. Returns false when
-// rho <= 0, T <= 0 or a NaN appears.
+// from the node's moments m = M f and ir = 1 / m[0]; A = d_x u_x - d_y u_y
+// and B = d_x u_y + d_y u_x. Returns false when rho <= 0, T <= 0 or a NaN
+// appears.
 template <int VER>
-LBM_HD bool collide_from_moments(const Hot& c, const double* m, double ir, const NbrVel& nv, double* df) {
+LBM_HD bool collide_from_moments(const Hot& c, const double* m, double ir, double A, double B, double* df) {
   const double rho = m[0], jx = m[1], jy = m[2], e = m[3];
   double q[16];
-  equilibrium_moments<VER, double>(rho, jx, jy, e, q);
+  equilibrium_moments<VER, double>(rho, ir, jx, jy, e, q);
   double col[16];
 #pragma unroll
   for (int k = 4; k < 16; ++k) col[k] = c.cq[k - 4] * (m[k] - q[k]);
   const double ux = jx * ir, uy = jy * ir;
-  const double T = e * ir - 0.5 * (ux * ux + uy * uy);
-  {
-    // energy-flux modification; its coefficients are exactly 0 for the
-    // unmodified model, so the terms then add exactly 0 (no branch)
-    const double A = (nv.ux_xp - nv.ux_xm) * c.inv2dx - (nv.uy_yp - nv.uy_ym) * c.inv2dy;
-    const double B = (nv.uy_xp - nv.uy_xm) * c.inv2dx + (nv.ux_yp - nv.ux_ym) * c.inv2dy;
-    const double rT = rho * T;
-    col[6] += c.cmod[0] * rT * ux * A + c.cmod[1] * rT * uy * B;
-    col[7] += c.cmod[2] * rT * ux * B + c.cmod[3] * rT * uy * A;
-  }
+  const double rT = e - 0.5 * mad(jx, ux, jy * uy);  // rho T
+  // energy-flux modification; its coefficients are exactly 0 for the
+  // unmodified model, so the terms then add exactly 0 (no branch)
+  const double tx = rT * ux, ty = rT * uy;
+  const double xA = tx * A, xB = tx * B, yA = ty * A, yB = ty * B;
+  col[6] = mad(c.cmod[1], yB, mad(c.cmod[0], xA, col[6]));
+  col[7] = mad(c.cmod[3], yA, mad(c.cmod[2], xB, col[7]));
   f_from_nonconserved(col, df);
-  return (rho > 0.0) && (T > 0.0);
+  return (rho > 0.0) && (rT > 0.0);
 }
 
-// The same from the distributions f.
+// The same from the distributions f and the neighbours' velocities.
 template <int VER>
 LBM_HD bool collide_delta(const Hot& c, const double* f, const NbrVel& nv, double* df) {
   double m[16];
   moments_from_f(f, m);
-  return collide_from_moments<VER>(c, m, 1.0 / m[0], nv, df);
-}
-
-// The collision added to the convection increments `acc`; the new
-// distributions f + (acc + df) are written to `acc`.
-template <int VER>
-LBM_HD bool collide_add(const Hot& c, const double* f, const NbrVel& nv, double* acc) {
-  double df[16];
-  const bool ok = collide_delta<VER>(c, f, nv, df);
-#pragma unroll
-  for (int i = 0; i < 16; ++i) acc[i] = f[i] + (acc[i] + df[i]);
-  return ok;
+  const double A = mad(nv.ux_xp - nv.ux_xm, c.inv2dx, -((nv.uy_yp - nv.uy_ym) * c.inv2dy));
+  const double B = mad(nv.uy_xp - nv.uy_xm, c.inv2dx, (nv.ux_yp - nv.ux_ym) * c.inv2dy);
+  return collide_from_moments<VER>(c, m, recip(m[0]), A, B, df);
 }
 
 // New distributions at one interior node.
 template <int VER>
 LBM_HD bool node_update(const Hot& c, const double* f, const double* fxp, const double* fxm, const double* fyp,
                         const double* fym, const NbrVel& nv, double* out) {
+  const bool ok = collide_delta<VER>(c, f, nv, out);
   ConvAll<0>::run(c, f, fxp, fxm, fyp, fym, out);
-  return collide_add<VER>(c, f, nv, out);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) out[i] += f[i];
+  return ok;
 }
 
 // Non-equilibrium extrapolation wall node from its fluid neighbour's new
@@ -212,14 +206,18 @@ template <int VER>
 LBM_HD void neq_wall(const double* wall, const double* fn, double* fw) {
   double m[16];
   moments_from_f(fn, m);
-  const double rho = m[0], ir = 1.0 / rho;
-  const double ux = m[1] * ir, uy = m[2] * ir;
-  const double T = m[3] * ir - 0.5 * (ux * ux + uy * uy);
-  double ew[16], en[16];
-  equilibrium_f<VER>(rho, wall[1], wall[2], wall[3], ew);
-  equilibrium_f<VER>(rho, ux, uy, T, en);
+  const double rho = m[0], ir = recip(rho);
+  const double uwx = wall[1], uwy = wall[2], ew = wall[3] + 0.5 * (uwx * uwx + uwy * uwy);
+  // the two equilibria differ in their moments only, so one back-transform
+  // serves both
+  double qw[16], qn[16];
+  equilibrium_moments<VER, double>(rho, ir, rho * uwx, rho * uwy, rho * ew, qw);
+  equilibrium_moments<VER, double>(rho, ir, m[1], m[2], m[3], qn);
 #pragma unroll
-  for (int i = 0; i < 16; ++i) fw[i] = ew[i] + (fn[i] - en[i]);
+  for (int k = 0; k < 16; ++k) qw[k] -= qn[k];
+  reconstruct<true>(qw, fw);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) fw[i] += fn[i];
 }
 
 }  // namespace lbm
