@@ -31,20 +31,14 @@ struct LineChunk {
   int pad[3];
 };
 
-// Ghost of line end `end` (0 low, 1 high) from the end node's distributions.
-__device__ __forceinline__ void line_ghost(const LineInst& I, const Hot& c, int end, const double* fe, double* g) {
-  const int side = 2 * I.axis + end;
-  const int kind = c.bc[side];
-  if (kind == BC_SPECULAR) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) g[i] = I.axis == 0 ? fe[MIRROR_X[i]] : fe[MIRROR_Y[i]];
-  } else if (kind == BC_DIRICHLET_EQ) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) g[i] = I.cold.ghost[side][i];
-  } else {  // zero-gradient (periodic lines are handled by wrapping inside the region)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) g[i] = fe[i];
-  }
+// Adds convection along AXIS to acc (the node's collision), each neighbour
+// value read from the region (entries e - 1, e + 1 beside the node's e) as it
+// is used, and acc to the node's distributions f.
+template <int I, int AXIS, int W, class C>
+__device__ __forceinline__ void line_convect(C& c, const double (*buf)[W], int e, double* f, const double* acc) {
+  constexpr bool moves = (AXIS == 0 ? VX[I] : VY[I]) != 0;
+  f[I] += convect_axis<I, AXIS>(c, acc[I], f[I], moves ? buf[I][e + 1] : 0.0, moves ? buf[I][e - 1] : 0.0);
+  if constexpr (I < 15) line_convect<I + 1, AXIS, W>(c, buf, e, f, acc);
 }
 
 // One chunk (index ci of the chunk list) for up to h steps from step n0 of
@@ -53,13 +47,25 @@ __device__ __forceinline__ void line_ghost(const LineInst& I, const Hot& c, int 
 // also takes the workgroup's next ticket from *ctr once the chunk is loaded
 // (so that the atomic's latency hides behind the time steps) and leaves it
 // in *tk_out (LDS) at the end.
+//
+// The region is held once and updated in place: every node is computed into
+// registers, and after a barrier written over the old one. Bound by FP64
+// issue, its latency and LDS traffic, the kernel needs waves: one buffer (37
+// KB at region 256) and at most 168 registers give three waves per SIMD where
+// two buffers gave two, a node's own distributions and moments stay in
+// registers from step to step, and the coefficients come through the scalar
+// cache: 512 lines, 656 k nodes, 200 steps in 2.24 ms against 2.88 for two
+// buffers at two waves and LDS coefficients (2.39 with three waves alone; four
+// waves spill: 2.32 persistent, 3.23 with a launch per block).
 template <int VER, int REGION, bool TICKET = false>
 __device__ __forceinline__ bool line_chunk(const double* __restrict__ A, double* __restrict__ B,
                                            const LineInst* __restrict__ insts, const LineChunk* __restrict__ chunks,
                                            int ci, const int* __restrict__ budget, int n0, int h,
                                            unsigned long long* ctr = nullptr, unsigned long long* tk_out = nullptr) {
-  __shared__ double buf[2][NV][REGION];
-  __shared__ Hot hs;
+  // entries 0 and R + 1 beside the region's R nodes hold the ghosts of the
+  // line's ends (at other ends nothing that is still valid reads them)
+  constexpr int W = REGION + 2;
+  __shared__ double buf[NV][W];
   const LineChunk ch = chunks[ci];
   const LineInst& I = insts[ch.inst];
   const int t = threadIdx.x;
@@ -75,118 +81,127 @@ __device__ __forceinline__ bool line_chunk(const double* __restrict__ A, double*
       for (int i = 0; i < 16; ++i) B[off + (long long)i * stride + ch.start + r] = A[off + (long long)i * stride + ch.start + r];
     return true;
   }
-  stage_hot(&I.hot, &hs);
-  const Hot& c = hs;
-  const bool periodic = c.bc[2 * I.axis] == BC_PERIODIC;  // then the chunk is the whole line
+  const int axis = I.axis;
+  const int klo = I.hot.bc[2 * axis], khi = I.hot.bc[2 * axis + 1];
+  const bool periodic = klo == BC_PERIODIC;  // then the chunk is the whole line
   const int lo = periodic ? 0 : max(ch.start - steps, 0);
   const int hi = periodic ? N : min(ch.start + ch.len + steps, N);
   const int R = hi - lo;  // <= REGION (guaranteed by the chunking)
+  const int g = lo + t;   // line node of this thread
+  const int e = t + 1;    // its entry
+  const bool held = t < R;
+  const bool first = held && g == 0, last = held && g == N - 1;
+  const bool is_wall = (first && klo == BC_NEQ_WALL) || (last && khi == BC_NEQ_WALL);
 
-  // load the region and its velocities; each thread keeps its node's moments
-  // (and 1 / rho) from one step to the next, for the collision and for the
-  // velocity its neighbours read
-  double m[16], ir = 0.0;
-  if (t < R) {
-    double f[16];
+  // Ghost entry beside a line's end, from the end node's values (periodic:
+  // the entry at the other end, an image of this node; the ghost of a fixed
+  // state is written once, at the start).
+  auto put_ghost = [&](int slot, int kind, const double* f, double ux, double uy) {
+    if (kind == BC_SPECULAR && axis == 0) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) buf[MIRROR_X[i]][slot] = f[i];
+      buf[16][slot] = -ux;
+      buf[17][slot] = uy;
+    } else if (kind == BC_SPECULAR) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) buf[MIRROR_Y[i]][slot] = f[i];
+      buf[16][slot] = ux;
+      buf[17][slot] = -uy;
+    } else if (kind == BC_ZERO_GRADIENT || kind == BC_PERIODIC) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) buf[i][slot] = f[i];
+      buf[16][slot] = ux;
+      buf[17][slot] = uy;
+    }
+  };
+  // A node's distributions and velocity into its entry, and the ghosts it feeds.
+  auto put = [&](const double* f, double ux, double uy) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) buf[i][e] = f[i];
+    buf[16][e] = ux;
+    buf[17][e] = uy;
+    if (first) put_ghost(periodic ? R + 1 : 0, klo, f, ux, uy);
+    if (last) put_ghost(periodic ? 0 : R + 1, khi, f, ux, uy);
+  };
+
+  // load the region and its velocities; each thread keeps its node's
+  // distributions, their moments and 1 / rho from one step to the next, for
+  // the collision and for the velocity its neighbours read
+  double f[16], m[16], ir = 0.0;
+  if (held) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) f[i] = A[off + (long long)i * stride + lo + t];
     moments_from_f(f, m);
     ir = recip(m[0]);
+    put(f, m[1] * ir, m[2] * ir);
+  }
+  if (t < 2) {  // fixed-state ghosts
+    const int side = 2 * axis + t, slot = t == 0 ? 0 : R + 1;
+    if ((t == 0 ? klo : khi) == BC_DIRICHLET_EQ && (t == 0 ? lo == 0 : hi == N)) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) buf[0][i][t] = f[i];
-    buf[0][16][t] = m[1] * ir;
-    buf[0][17][t] = m[2] * ir;
+      for (int i = 0; i < 16; ++i) buf[i][slot] = I.cold.ghost[side][i];
+      buf[16][slot] = I.cold.gvel[side][0];
+      buf[17][slot] = I.cold.gvel[side][1];
+    }
   }
   __syncthreads();
   unsigned long long next = 0;
   if (TICKET && t == 0) next = __hip_atomic_fetch_add(ctr, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  const int g = lo + t;  // line node of this thread
-  const bool wall_lo = c.bc[2 * I.axis] == BC_NEQ_WALL, wall_hi = c.bc[2 * I.axis + 1] == BC_NEQ_WALL;
   bool ok = true;
-  int P = 0;
   for (int s = 0; s < steps; ++s) {
     // nodes valid after this step: the region shrinks at ends that are not physical
     const int vlo = (lo == 0) ? 0 : lo + s + 1;
     const int vhi = (hi == N) ? N : hi - s - 1;
-    const int Q = P ^ 1;
-    const bool is_wall = (wall_lo && g == 0) || (wall_hi && g == N - 1);
-    if (t < R && g >= vlo && g < vhi && !is_wall) {
-      double f[16], fm[16], fp[16];
-      double uxm, uym, uxp, uyp;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) f[i] = buf[P][i][t];
-      // neighbour below
-      if (g > 0 || periodic) {
-        const int r = (g > 0) ? t - 1 : R - 1;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) fm[i] = buf[P][i][r];
-        uxm = buf[P][16][r];
-        uym = buf[P][17][r];
-      } else {
-        line_ghost(I, c, 0, f, fm);
-        velocity_of(fm, uxm, uym);
-      }
-      if (g < N - 1 || periodic) {
-        const int r = (g < N - 1) ? t + 1 : 0;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) fp[i] = buf[P][i][r];
-        uxp = buf[P][16][r];
-        uyp = buf[P][17][r];
-      } else {
-        line_ghost(I, c, 1, f, fp);
-        velocity_of(fp, uxp, uyp);
-      }
+    const bool update = held && g >= vlo && g < vhi && !is_wall;
+    if (update) {
       // the step's arithmetic along the line's axis (the other axis's zero
       // terms left out), the collision from the kept moments
-      double out[16];
-      if (I.axis == 0) {
-        ok &= collide_from_moments<VER>(c, m, ir, (uxp - uxm) * c.inv2dx, (uyp - uym) * c.inv2dx, out);
-        ConvAxis<0, 0>::run(c, f, fp, fm, out);
+      ScalarHot& c = scalar_hot(&I.hot);
+      const double dux = buf[16][e + 1] - buf[16][e - 1], duy = buf[17][e + 1] - buf[17][e - 1];
+      double df[16];
+      if (axis == 0) {
+        ok &= collide_from_moments<VER>(c, m, ir, dux * c.inv2dx, duy * c.inv2dx, df);
+        line_convect<0, 0, W>(c, buf, e, f, df);
       } else {
-        ok &= collide_from_moments<VER>(c, m, ir, -((uyp - uym) * c.inv2dy), (uxp - uxm) * c.inv2dy, out);
-        ConvAxis<0, 1>::run(c, f, fp, fm, out);
+        ok &= collide_from_moments<VER>(c, m, ir, -(duy * c.inv2dy), dux * c.inv2dy, df);
+        line_convect<0, 1, W>(c, buf, e, f, df);
       }
-#pragma unroll
-      for (int i = 0; i < 16; ++i) out[i] += f[i];
-      moments_from_f(out, m);
+      moments_from_f(f, m);
       ir = recip(m[0]);
-#pragma unroll
-      for (int i = 0; i < 16; ++i) buf[Q][i][t] = out[i];
-      buf[Q][16][t] = m[1] * ir;
-      buf[Q][17][t] = m[2] * ir;
     }
+    __syncthreads();  // every node of this step has been read
+    if (update) put(f, m[1] * ir, m[2] * ir);
     __syncthreads();
     if (I.walls) {  // wall nodes from their neighbour's new distributions
-      if (t < R && is_wall) {
-        const int r = (g == 0) ? t + 1 : t - 1;
-        double fn[16], fw[16];
+      if (is_wall) {
+        const int r = first ? e + 1 : e - 1;
+        double fn[16];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) fn[i] = buf[Q][i][r];
-        neq_wall<VER>(I.cold.wall[2 * I.axis + (g == 0 ? 0 : 1)], fn, fw);
+        for (int i = 0; i < 16; ++i) fn[i] = buf[i][r];
+        neq_wall<VER>(I.cold.wall[2 * axis + (first ? 0 : 1)], fn, f);
         // its velocity as any node's (from its moments), so that it does not
         // depend on whether the next step reloads the node
-        moments_from_f(fw, m);
+        moments_from_f(f, m);
         ir = recip(m[0]);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) buf[Q][i][t] = fw[i];
-        buf[Q][16][t] = m[1] * ir;
-        buf[Q][17][t] = m[2] * ir;
+        for (int i = 0; i < 16; ++i) buf[i][e] = f[i];
+        buf[16][e] = m[1] * ir;
+        buf[17][e] = m[2] * ir;
       }
       __syncthreads();
     }
-    P = Q;
   }
   // write the chunk back
-  if (g >= ch.start && g < ch.start + ch.len && t < R) {
+  if (held && g >= ch.start && g < ch.start + ch.len) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) B[off + (long long)i * stride + g] = buf[P][i][t];
+    for (int i = 0; i < 16; ++i) B[off + (long long)i * stride + g] = f[i];
   }
   if (TICKET && t == 0) *tk_out = next;
   return ok;
 }
 
 template <int VER, int REGION>
-__global__ __launch_bounds__(REGION, 2) void k_batch_line(const double* __restrict__ A, double* __restrict__ B,
+__global__ __launch_bounds__(REGION, 3) void k_batch_line(const double* __restrict__ A, double* __restrict__ B,
                                                           const LineInst* __restrict__ insts,
                                                           const LineChunk* __restrict__ chunks,
                                                           const int* __restrict__ budget, int n0, int h,
@@ -232,7 +247,7 @@ __global__ void k_persist_reset(unsigned long long* ctr, int* epoch, int n) {
 // the host reports the error and the state is then invalid.
 // status: health flag at word 0, error word at 16, ticket counter at 32.
 template <int VER, int REGION>
-__global__ __launch_bounds__(REGION, 2) void k_batch_line_persistent(double* src, double* dst,
+__global__ __launch_bounds__(REGION, 3) void k_batch_line_persistent(double* src, double* dst,
                                                                const LineInst* __restrict__ insts,
                                                                const LineChunk* __restrict__ chunks, int nchunks,
                                                                const int* __restrict__ budget, int nsteps, int h,

@@ -36,6 +36,24 @@ struct Cold {
   double gvel[4][2];    // velocities of the ghosts
 };
 
+// Coefficients read through the scalar cache: a reference whose loads the
+// compiler makes scalar (constant address space, wave-uniform pointer) and,
+// because the pointer is new at each call, repeats where it is taken instead
+// of keeping 50 scalar registers alive across a kernel's loop. Beside reads
+// from LDS, where one 16-byte broadcast to a wave takes the pipe eight cycles,
+// the reads cost the vector units nothing.
+#if defined(__HIP_DEVICE_COMPILE__)
+typedef const __attribute__((address_space(4))) Hot ScalarHot;
+__device__ __forceinline__ ScalarHot& scalar_hot(const Hot* p) {
+  ScalarHot* q = (ScalarHot*)(unsigned long long)p;
+  asm volatile("" : "+s"(q));
+  return *q;
+}
+#else
+typedef const Hot ScalarHot;
+LBM_HD ScalarHot& scalar_hot(const Hot* p) { return *p; }
+#endif
+
 // Neighbour velocities the modification needs.
 struct NbrVel {
   double ux_xp, uy_xp, ux_xm, uy_xm;  // at x+1, x-1
@@ -132,10 +150,10 @@ struct ConvAll<16> {
 // The same along one axis only (AXIS 0: x, 1: y), for a node whose
 // neighbours along the other axis are itself (a one-dimensional problem:
 // those terms are exact zeros, left out).
-template <int I, int AXIS>
-LBM_HD double convect_axis(const Hot& c, double v, double f, double fp, double fm) {
+template <int I, int AXIS, class C>
+LBM_HD double convect_axis(C& c, double v, double f, double fp, double fm) {
   constexpr int vel = AXIS == 0 ? VX[I] : VY[I], k = vel < 0 ? -vel : vel;
-  const double* l = AXIS == 0 ? c.lx : c.ly;
+  auto* l = AXIS == 0 ? c.lx : c.ly;
   if constexpr (k != 0) {
     v = mad(l[2 * (k - 1) + (vel > 0 ? 0 : 1)], fp - f, v);
     v = mad(l[2 * (k - 1) + (vel > 0 ? 1 : 0)], fm - f, v);
@@ -143,24 +161,12 @@ LBM_HD double convect_axis(const Hot& c, double v, double f, double fp, double f
   return v;
 }
 
-template <int I, int AXIS>
-struct ConvAxis {
-  LBM_HD static void run(const Hot& c, const double* f, const double* fp, const double* fm, double* acc) {
-    acc[I] = convect_axis<I, AXIS>(c, acc[I], f[I], fp[I], fm[I]);
-    ConvAxis<I + 1, AXIS>::run(c, f, fp, fm, acc);
-  }
-};
-template <int AXIS>
-struct ConvAxis<16, AXIS> {
-  LBM_HD static void run(const Hot&, const double*, const double*, const double*, double*) {}
-};
-
 // Collision of one node in velocity space, -dt M^-1 Q (Sec. II), into df,
 // from the node's moments m = M f and ir = 1 / m[0]; A = d_x u_x - d_y u_y
 // and B = d_x u_y + d_y u_x. Returns false when rho <= 0, T <= 0 or a NaN
 // appears.
-template <int VER>
-LBM_HD bool collide_from_moments(const Hot& c, const double* m, double ir, double A, double B, double* df) {
+template <int VER, class C>
+LBM_HD bool collide_from_moments(C& c, const double* m, double ir, double A, double B, double* df) {
   const double rho = m[0], jx = m[1], jy = m[2], e = m[3];
   double q[16];
   equilibrium_moments<VER, double>(rho, ir, jx, jy, e, q);
