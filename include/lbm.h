@@ -135,23 +135,23 @@ lbm_status lbm_set_f(lbm_handle* h, const double* d_f);
 lbm_status lbm_check(lbm_handle* h);
 
 /* Kernel variant used by lbm_step:
- *   0 the fused LDS-staged kernel, one launch per step (default for grids of
- *     more than 512 nodes and more than 16 rows, and for scheme 1);
+ *   0 the fused LDS-staged kernel, one launch per step (default for
+ *     scheme 1 on any grid, and with NEQ walls above 262144 nodes);
  *   1 the plain one-thread-per-node global-memory kernel (a reference for
  *     race and indexing checks);
  *   2 the small-grid kernel (default when nx ny <= 512 and scheme 0;
  *     LBM_EINVAL otherwise): one workgroup holds the whole grid in LDS and
  *     takes up to 65536 steps per launch;
  *   3 the windowed kernel (scheme 0 and nx ny > 512, LBM_EINVAL otherwise;
- *     default when ny <= 16): workgroups hold overlapping windows of the grid
+ *     default when ny <= 16 and up to 196608 nodes, 262144 with NEQ walls):
+ *     workgroups hold overlapping windows of the grid
  *     in LDS (lbm_set_window) and take several steps per launch,
  *     recomputing the overlap;
  *   4 the fused kernel taking two time steps per launch (scheme 0 without
- *     NEQ walls, LBM_EINVAL otherwise; default when the two distribution
- *     buffers take more than 512 MB): the intermediate level stays in LDS,
+ *     NEQ walls, LBM_EINVAL otherwise; default above 196608 nodes): the intermediate level stays in LDS,
  *     so each node's distributions cross HBM once per two steps; an odd
  *     last step of a call takes variant 0.
- * Variants 2 and 3 take many steps per launch, so small and narrow grids are
+ * Variants 2 and 3 take many steps per launch, so small and medium grids are
  * not bound by launch cost. All variants give the same results to rounding.
  * lbm_set_tile sets the tile shape of the current variant (0, or 4 for the
  * two-step kernel, whose shape is kept separately): rows per workgroup tile
@@ -176,8 +176,10 @@ lbm_status lbm_get_store_mode(const lbm_handle* h, int32_t* nontemporal);
  * window is held whole; a longer one is cut into windows that overlap by
  * `steps` nodes on each cut side, each writing its middle (extent - 2 steps)
  * nodes, so cut extents must exceed 2 steps. Default: grids of <= 16 rows
- * take every row and 64 columns (32 when ny > 8) with steps = columns / 8;
- * other grids 32 x 16 with 2 steps. Results do not depend on the shape
+ * take every row and 64 columns (32 when ny > 8) with 12 steps, or columns /
+ * 8 steps where 12 need more rounds of workgroups; other grids 16 x 16 with
+ * 4 steps, 32 x 16 with 4 or 3 while that makes at most 256 windows, else
+ * 16 x 16 with 3. Results do not depend on the shape
  * beyond rounding. */
 lbm_status lbm_set_window(lbm_handle* h, int32_t cols, int32_t rows, int32_t steps);
 lbm_status lbm_get_window(const lbm_handle* h, int32_t* cols, int32_t* rows, int32_t* steps);

@@ -105,6 +105,15 @@ static hipError_t step_into(lbm_adjoint* a, const double* fin, double* fout) {
                      default_tile(a->p.nx, a->p.ny), a->flag(), a->stream);
 }
 
+// Rows per tile of the LDS-staged adjoint step: the tallest of 64, 32, ... 4
+// that leaves 1024 tiles of 64 columns.
+static int adjoint_rows(int nx, int ny) {
+  const long long strips = (nx + STRIP - 1) / STRIP;
+  int rows = 64;
+  while (rows > WAVES && strips * ((ny + rows - 1) / rows) < 1024) rows /= 2;
+  return rows;
+}
+
 extern "C" {
 
 size_t lbm_adjoint_workspace_bytes(const lbm_params* p, int64_t nsteps, int32_t ckpt_interval) {
@@ -134,7 +143,7 @@ lbm_status lbm_adjoint_create(const lbm_params* p, int64_t nsteps, int32_t ckpt_
   // it takes 507 us per step against 598 for the gather form); small grids
   // give each tile one row per wavefront, and the gather form is faster
   // there (12.9 against 15.8 us per step at 512 x 128)
-  a->variant = default_tile(p->nx, p->ny).rows >= 16 ? 0 : 1;
+  a->variant = adjoint_rows(p->nx, p->ny) >= 16 ? 0 : 1;
   make_coef(p, &a->host.hot, &a->host.cold);
   std::memset(&a->adj, 0, sizeof(a->adj));
   const double dt = p->dt, s5 = p->s[4], s6 = p->s[5], s7 = p->s[6], s8 = p->s[7];
@@ -240,7 +249,7 @@ lbm_status lbm_adjoint_backward(lbm_adjoint* a, const double* d_rho0, const doub
   // the LDS-staged step: 64-column tiles of 4 waves (at least 4 rows each, so
   // there are no more tiles than the per-block partial slots)
   auto kfused = ver == 2 ? k_adj_fused<2, 4, true> : ver == 3 ? k_adj_fused<3, 4, true> : k_adj_fused<1, 4, true>;
-  const MarchGeom ag = march_geom(a->p.nx, a->p.ny, TileShape{std::max(4, default_tile(a->p.nx, a->p.ny).rows), 4, 1});
+  const MarchGeom ag = march_geom(a->p.nx, a->p.ny, TileShape{adjoint_rows(a->p.nx, a->p.ny), 4, 1});
   for (int k = L.K - 1; k >= 0; --k) {
     const int64_t n0 = (int64_t)k * L.C, n1 = std::min<int64_t>(n0 + L.C, a->nsteps);
     // recompute f^{n0+1} .. f^{n1-1} into the segment store (f^{n0} is the checkpoint)

@@ -201,30 +201,52 @@ hipError_t launch_step2(const Field& F, const Hot* c, const Cold* cold, int vers
   return hipGetLastError();
 }
 
-TileShape default_tile2(int nx, int ny) {
-  // two waves per workgroup (two workgroups per CU), and tiles tall enough
-  // to leave just under two per workgroup slot (512 slots): the tuner's
-  // pick at 4096 x 1024 (70-row tiles, 164 us per step against 178 for
-  // 16-row tiles); heights rounded up to even
-  const long long strips = (nx + OSTRIP - 1) / OSTRIP;
-  const long long segs = std::max(1ll, 1024 / strips);
-  int rows = (int)std::min<long long>(1024, (ny + segs - 1) / segs);
-  rows = std::max(2, (rows + 1) / 2 * 2);
+// Ordinary stores while both buffers (256 bytes per node) take between 32
+// and 512 MB (measured per step: faster at 1024 x 256 and 2048 x 512, slower
+// at 512 x 128 and 4096 x 1024).
+static int default_nt(int nx, int ny) {
   const long long bytes = (long long)nx * ny * 256;
-  const int nt = (bytes > (32ll << 20) && bytes <= (512ll << 20)) ? 0 : 1;
-  return TileShape{rows, 2, nt};
+  return (bytes > (32ll << 20) && bytes <= (512ll << 20)) ? 0 : 1;
 }
 
-// Default kernel of a problem: the whole grid in one workgroup when it fits,
-// windows for narrow grids, two steps per launch where both distribution
-// buffers exceed the 256 MB last-level cache (the step is then bound by HBM,
-// and the two-step kernel halves its traffic), else the one-step kernel.
+// Tiles of two waves, two workgroups per CU: 512 run at a time, so a step
+// takes ceil(tiles / 512) rounds of a tile's time, which measured
+// proportional to rows + 5.5 (the marching start-up). The height (even, at
+// most 128) of the fewest rounds x rows: one round of 10 rows at 1024 x 256
+// (15.8 us per step; 8 rows, two rounds: 23.1), of 36 at 2048 x 512 (43.3;
+// 32 rows: 73.5), of 72 at 2048 x 1024 (82.8; 64 rows: 138.7), two of 72 at
+// 4096 x 1024 (154; 64 rows: 195).
+TileShape default_tile2(int nx, int ny) {
+  const long long strips = (nx + OSTRIP - 1) / OSTRIP;
+  int best = 2;
+  double cost = 1e300;
+  for (int rows = 2; rows <= 128; rows += 2) {
+    const long long tiles = strips * ((ny + rows - 1) / rows);
+    const double t = (double)((tiles + 511) / 512) * (rows + 5.5);
+    if (t < cost) cost = t, best = rows;
+  }
+  return TileShape{best, 2, default_nt(nx, ny)};
+}
+
+// Default kernel of a problem. The whole grid in one workgroup when it fits;
+// windows for narrow grids and up to 196 608 nodes (262 144 with NEQ walls,
+// which the two-step kernel does not take): several steps per launch, while
+// the overlap they recompute costs less than the launches and the short
+// tiles of the others (per step, windows against the better of the one- and
+// two-step kernels at their best tiles: 3.2 against 6.8 us at 256 x 64, 5.2
+// against 7.1 at 600 x 100, 8.9 against 11.7 at 400 x 300; 16.1 against 15.8
+// at 1024 x 256, 23.2 against 20.0 at 1000 x 400; with walls 8.8 against
+// 13.2 at 400 x 200, 19.5 against 20.2 at 600 x 400). Above that two steps
+// per launch, which halve the traffic per step (against one step: 34.4 and
+// 35.1 us at 1448 x 512, 82.8 and 111 at 2048 x 1024), or one step with NEQ
+// walls or the flux-limited scheme.
 int default_variant(const lbm_params* p) {
   if (small_problem(p)) return 2;
   if (narrow_problem(p)) return 3;
-  const long long bytes = (long long)p->nx * p->ny * 256;
-  if (two_step_problem(p) && bytes > (512ll << 20)) return 4;
-  return 0;
+  const long long nodes = (long long)p->nx * p->ny;
+  const bool two = two_step_problem(p);
+  if (window_problem(p) && nodes <= (two ? 3ll << 16 : 1ll << 18)) return 3;
+  return two ? 4 : 0;
 }
 
 // True when the whole grid fits the one-workgroup multi-step kernel.
@@ -248,7 +270,7 @@ hipError_t launch_small(const Field& F, const Hot* c, const Cold* cold, int vers
 // small-grid kernel.
 bool window_problem(const lbm_params* p) { return p->scheme == 0 && !small_problem(p); }
 
-// True when the windowed kernel is the default: narrow grids (<= 16 rows).
+// Narrow grids (<= 16 rows): windows hold every row.
 bool narrow_problem(const lbm_params* p) { return window_problem(p) && p->ny <= 16; }
 
 // One axis of the window shape: the whole axis in one window when it fits,
@@ -287,53 +309,82 @@ bool make_window(const lbm_params* p, int wc, int wr, int h, WinGeom* g) {
   return true;
 }
 
-// Default window shape: narrow grids take every row and 64 columns (32 when
-// ny > 8), h = columns / 8; other grids 32 x 16 nodes, h = 2.
+// Windows that run at a time: three workgroups of up to 256 nodes per CU, two
+// of up to 384, one of up to 512 (by the registers of launch_window's
+// instances).
+static long long window_rounds(const WinGeom& g) {
+  const int threads = (g.x.w * g.y.w + 63) / 64 * 64;
+  const long long slots = 256ll * (threads <= 256 ? 3 : threads <= 384 ? 2 : 1);
+  return ((long long)g.x.nwin * g.y.nwin + slots - 1) / slots;
+}
+
+// Default window shape. A launch costs about 5 us beside its steps, so more
+// steps per launch pay until the overlap takes another round of workgroups.
+// Narrow grids: every row, 64 columns (32 when ny > 8), 12 steps where that
+// takes no more rounds than columns / 8 steps, else columns / 8 (per step:
+// 1.86 against 2.05 us at 2000 x 4, 2.97 against 3.99 at 2000 x 16, 5.64
+// against 6.25 at 20000 x 8). Others: the first of 16 x 16 nodes with 4
+// steps, 32 x 16 with 4 and 32 x 16 with 3 that gives every window a CU of
+// its own (a lone workgroup per CU takes its steps at the latency of one
+// node update per wave: 3.2 us per step at 256 x 64, 4.1 at 130 x 96, 5.2 at
+// 600 x 100), else 16 x 16 with 3, three windows per CU (8.9 at 400 x 300;
+// 24 x 10 nodes with 2 steps: 9.8).
 WinGeom default_window(const lbm_params* p) {
   WinGeom g{};
   if (p->ny <= 16) {
     const int wc = p->ny <= 8 ? 64 : 32;
     make_window(p, wc, p->ny, wc / 8, &g);
-  } else {
-    make_window(p, 32, 16, 2, &g);
+    WinGeom g12;
+    if (make_window(p, wc, p->ny, 12, &g12) && window_rounds(g12) <= window_rounds(g)) g = g12;
+    return g;
   }
+  const int shapes[][3] = {{16, 16, 4}, {32, 16, 4}, {32, 16, 3}};
+  for (const auto& c : shapes)
+    if (make_window(p, c[0], c[1], c[2], &g) && (long long)g.x.nwin * g.y.nwin <= 256) return g;
+  make_window(p, 16, 16, 3, &g);
   return g;
 }
 
 hipError_t launch_window(const Field& F, const Hot* c, const Cold* cold, int version, bool walls,
                          const WinGeom& g, int nsteps, int* flag, hipStream_t s) {
+  // the smallest instance that holds the window (its LDS and registers decide
+  // how many workgroups share a CU)
   decltype(&k_step_window<1, false, SMALL_NODES>) k;
   const int threads = (g.x.w * g.y.w + 63) / 64 * 64;
-  if (threads <= SMALL_NODES / 2) {  // half the LDS: two workgroups per CU
-    if (walls)
-      k = version == 2 ? k_step_window<2, true, SMALL_NODES / 2>
-                       : version == 3 ? k_step_window<3, true, SMALL_NODES / 2> : k_step_window<1, true, SMALL_NODES / 2>;
-    else
-      k = version == 2 ? k_step_window<2, false, SMALL_NODES / 2>
-                       : version == 3 ? k_step_window<3, false, SMALL_NODES / 2>
-                                      : k_step_window<1, false, SMALL_NODES / 2>;
-  } else if (walls) {
-    k = version == 2 ? k_step_window<2, true, SMALL_NODES>
-                     : version == 3 ? k_step_window<3, true, SMALL_NODES> : k_step_window<1, true, SMALL_NODES>;
+#define LBM_WINDOW(WALLS, NODES)                                                                     \
+  k = version == 2 ? k_step_window<2, WALLS, NODES> : version == 3 ? k_step_window<3, WALLS, NODES> \
+                                                                   : k_step_window<1, WALLS, NODES>
+  if (threads <= 256) {
+    if (walls) LBM_WINDOW(true, 256); else LBM_WINDOW(false, 256);
+  } else if (threads <= 384) {
+    if (walls) LBM_WINDOW(true, 384); else LBM_WINDOW(false, 384);
   } else {
-    k = version == 2 ? k_step_window<2, false, SMALL_NODES>
-                     : version == 3 ? k_step_window<3, false, SMALL_NODES> : k_step_window<1, false, SMALL_NODES>;
+    if (walls) LBM_WINDOW(true, SMALL_NODES); else LBM_WINDOW(false, SMALL_NODES);
   }
+#undef LBM_WINDOW
   hipLaunchKernelGGL(k, dim3(g.x.nwin * g.y.nwin), dim3(threads), 0, s, F, c, cold, g, nsteps, flag);
   return hipGetLastError();
 }
 
+// Tiles of four waves, two workgroups per CU: a step takes full rounds of 512
+// tiles and a last one, which costs half as much when its tiles have a CU
+// each (at most 256). The height (a multiple of 4, at most 64) of the least
+// total; the constants are the start-up of a tile in rows, with and without
+// a second workgroup on its CU. Measured per step: 16 rows (512 tiles) 32.6
+// us at 1000 x 500 with walls, 8 rows (1008 tiles) 34.0, 20 rows (400) 36.0;
+// the flux-limited scheme at 2048 x 512 with 32 rows (512) 79.5, 16 rows
+// 85.1, 36 rows 84.4, and at 1023 x 257 with 20 rows (208) 34.3, 4 rows
+// (1040) 39.0.
 TileShape default_tile(int nx, int ny) {
-  // tall tiles amortise the two halo rows; keep at least ~2 workgroups per CU
   const long long strips = (nx + STRIP - 1) / STRIP;
-  int rows = 64;
-  while (rows > WAVES && strips * ((ny + rows - 1) / rows) < 1024) rows /= 2;
-  // ordinary stores while both buffers (256 bytes per node) take between 32
-  // and 512 MB (measured per step: faster at 1024 x 256 and 2048 x 512,
-  // slower at 512 x 128 and 4096 x 1024)
-  const long long bytes = (long long)nx * ny * 256;
-  const int nt = (bytes > (32ll << 20) && bytes <= (512ll << 20)) ? 0 : 1;
-  return TileShape{rows, WAVES, nt};
+  int best = WAVES;
+  long long cost = -1;
+  for (int rows = WAVES; rows <= 64; rows += WAVES) {
+    const long long tiles = strips * ((ny + rows - 1) / rows), last = tiles % 512;
+    const long long t = (tiles / 512) * 2 * (rows + 6) + (last == 0 ? 0 : last <= 256 ? rows + 14 : 2 * (rows + 6));
+    if (cost < 0 || t < cost) cost = t, best = rows;
+  }
+  return TileShape{best, WAVES, default_nt(nx, ny)};
 }
 
 }  // namespace lbm
@@ -692,11 +743,12 @@ lbm_status lbm_tune(lbm_handle* h, int64_t probe_steps, double* d_scratch, size_
     int ns = 0;
     if (h->p.ny <= 16) {
       for (int wc = 32; wc <= SMALL_NODES; wc *= 2)
-        for (int div : {16, 8, 4})
-          if (ns < 24) shapes[ns][0] = wc, shapes[ns][1] = h->p.ny, shapes[ns][2] = wc / div, ++ns;
+        for (int steps : {wc / 16, wc / 8, 12, wc / 4})
+          if (ns < 24) shapes[ns][0] = wc, shapes[ns][1] = h->p.ny, shapes[ns][2] = steps, ++ns;
     } else {
       const int two_d[][3] = {{32, 16, 2}, {32, 16, 3}, {16, 32, 2}, {16, 32, 3},
-                              {32, 8, 2},  {64, 8, 2},  {16, 16, 2}, {16, 16, 3}};
+                              {32, 8, 2},  {64, 8, 2},  {16, 16, 2}, {16, 16, 3},
+                              {16, 16, 4}, {32, 16, 4}, {24, 16, 4}, {24, 10, 2}};
       for (const auto& c3 : two_d) shapes[ns][0] = c3[0], shapes[ns][1] = c3[1], shapes[ns][2] = c3[2], ++ns;
     }
     h->variant = 3;

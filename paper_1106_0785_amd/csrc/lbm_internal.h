@@ -46,6 +46,7 @@ int default_variant(const lbm_params* p);
 // Small-grid and windowed kernels (lbm_multistep.h) and their selection
 // rules, as lbm_create applies them.
 bool small_problem(const lbm_params* p);
+bool window_problem(const lbm_params* p);
 bool narrow_problem(const lbm_params* p);
 WinGeom default_window(const lbm_params* p);
 hipError_t launch_small(const Field& F, const Hot* c, const Cold* cold, int version, bool walls, int nsteps,

@@ -175,14 +175,42 @@ __device__ __forceinline__ Src win_nbr(const WinSpan& sp, int w, int g, int d, i
   return sg;
 }
 
-// NODES: most nodes a window holds (512, or 256 so that two workgroups
-// share a CU's LDS).
+// Convection of all 16 velocities of a windowed node added to acc, and acc to
+// the node's distributions f; the neighbour values are read from the window as
+// they are used (entries kxp .. kym; a ghost without a mirror is an entry too).
+// MIR: some lane's neighbour is a mirror ghost, its own entry with the planes
+// mirrored (flags bit 0 x+1, 1 x-1, 2 y+1, 3 y-1).
+template <int I, bool MIR, int W>
+__device__ __forceinline__ void window_convect(const Hot& c, const double (*buf)[W], int kxp, int kxm, int kyp,
+                                               int kym, int flags, double* f, const double* acc) {
+  auto at = [&](int k, int bit, int mirror) {
+    if constexpr (MIR) return buf[(flags & bit) ? mirror : I][k];
+    return buf[I][k];
+  };
+  f[I] += convect<I>(c, acc[I], f[I], VX[I] ? at(kxp, 1, MIRROR_X[I]) : 0.0, VX[I] ? at(kxm, 2, MIRROR_X[I]) : 0.0,
+                     VY[I] ? at(kyp, 4, MIRROR_Y[I]) : 0.0, VY[I] ? at(kym, 8, MIRROR_Y[I]) : 0.0);
+  if constexpr (I < 15) window_convect<I + 1, MIR, W>(c, buf, kxp, kxm, kyp, kym, flags, f, acc);
+}
+
+// NODES: most nodes a window holds. The window is held once and updated in
+// place (every node computed into registers, then written over the old one
+// after a barrier), and a thread keeps its node's distributions and moments
+// in registers, so a step reads the 48 neighbour values only. One LDS copy and
+// at most 168 registers (up to 384 nodes) let three waves share a SIMD where
+// two copies left one or two. Bound by the latency of the node update at one
+// wave per SIMD and by FP64 issue at three. Per step, against two copies and
+// the moments formed again from LDS (same shapes): 3.5 against 3.9 us at
+// 60 x 40 with walls, 6.6 against 8.8 at 512 x 128 (both 16 x 16 nodes, 4
+// steps), 9.2 against 11.9 at 400 x 300 (16 x 16, 3 steps), 2.1 against 2.6
+// at 2000 x 4 (64 x 4, 8 steps).
 template <int VER, bool WALLS, int NODES>
-__global__ __launch_bounds__(NODES) void k_step_window(Field F, const Hot* __restrict__ hot,
+__global__ __launch_bounds__(NODES, NODES <= 384 ? 3 : 2) void k_step_window(Field F, const Hot* __restrict__ hot,
                                                       const Cold* __restrict__ cold, WinGeom wg, int nsteps,
                                                       int* flag) {
-  // 16 distributions and the velocity of every held node, two buffers
-  __shared__ double buf[2][NV][NODES];
+  // 16 distributions and the velocity of every held node, and the ghosts of
+  // the four sides' fixed states
+  constexpr int W = NODES + 4;
+  __shared__ double buf[NV][W];
   __shared__ Hot hs;
   stage_hot(hot, &hs);
   const Hot& c = hs;
@@ -195,42 +223,36 @@ __global__ __launch_bounds__(NODES) void k_step_window(Field F, const Hot* __res
   const int xv = sx.s + xw, yv = sy.s + yw;  // virtual on a periodic cut axis
   const int xg = xper ? ((xv % F.nx) + F.nx) % F.nx : xv;
   const int yg = yper ? ((yv % F.ny) + F.ny) % F.ny : yv;
-  // a node's distributions and velocity into buffer b
-  auto put = [&](int b, const double* f) {
-    double ux, uy;
-    velocity_of(f, ux, uy);
+  const long long at = (long long)yg * F.pitch + xg;
+  auto put = [&](const double* f, double ux, double uy) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) buf[b][i][t] = f[i];
-    buf[b][16][t] = ux;
-    buf[b][17][t] = uy;
+    for (int i = 0; i < 16; ++i) buf[i][t] = f[i];
+    buf[16][t] = ux;
+    buf[17][t] = uy;
   };
+  double f[16], m[16], ir = 0.0;
   if (active) {
-    double f[16];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) f[i] = F.fin[i * F.plane + (long long)yg * F.pitch + xg];
-    put(0, f);
+    for (int i = 0; i < 16; ++i) f[i] = F.fin[at + i * F.plane];
+    moments_from_f(f, m);
+    ir = recip(m[0]);
+    put(f, m[1] * ir, m[2] * ir);
   }
-  __syncthreads();
+  for (int k = t; k < 4 * NV; k += blockDim.x) {
+    const int side = k / NV, i = k % NV;
+    if (c.bc[side] == BC_DIRICHLET_EQ) buf[i][NODES + side] = i < 16 ? cold->ghost[side][i] : cold->gvel[side][i - 16];
+  }
   int lxp, lxm, lyp, lym;
   const Src nxp = win_nbr(sx, xw, xg, 1, F.nx, c.bc[0], c.bc[1], 0, lxp);
   const Src nxm = win_nbr(sx, xw, xg, -1, F.nx, c.bc[0], c.bc[1], 0, lxm);
   const Src nyp = win_nbr(sy, yw, yg, 1, F.ny, c.bc[2], c.bc[3], 2, lyp);
   const Src nym = win_nbr(sy, yw, yg, -1, F.ny, c.bc[2], c.bc[3], 2, lym);
-  const Src cx{xw, 0, -1}, cy{yw, 0, -1};
-  // a neighbour's distributions and velocity: the stored velocity, or, for
-  // a ghost point, the velocity of the ghost distributions
-  auto point = [&](int b, int lx, int ly, const Src& gx, const Src& gy, double* f, double& ux, double& uy) {
-    const int k = ly * sx.n + lx;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) f[i] = buf[b][i][k];
-    if ((gx.mode | gy.mode) != 0) {
-      fix_ghost(cold, gx, gy, f);
-      velocity_of(f, ux, uy);
-    } else {
-      ux = buf[b][16][k];
-      uy = buf[b][17][k];
-    }
-  };
+  const int kxp = nxp.mode == 2 ? NODES + nxp.side : yw * sx.n + lxp;
+  const int kxm = nxm.mode == 2 ? NODES + nxm.side : yw * sx.n + lxm;
+  const int kyp = nyp.mode == 2 ? NODES + nyp.side : lyp * sx.n + xw;
+  const int kym = nym.mode == 2 ? NODES + nym.side : lym * sx.n + xw;
+  const int flags = (nxp.mode == 1 ? 1 : 0) | (nxm.mode == 1 ? 2 : 0) | (nyp.mode == 1 ? 4 : 0) | (nym.mode == 1 ? 8 : 0);
+  const bool mirrors = __any(flags != 0);  // wave-uniform
   const bool wall = WALLS && active && is_wall_node(c, xg, yg, F.nx, F.ny);
   int wnb = 0, wside = 0;
   if (WALLS && wall) {
@@ -239,43 +261,57 @@ __global__ __launch_bounds__(NODES) void k_step_window(Field F, const Hot* __res
     else if (c.bc[0] == BC_NEQ_WALL && xg == 0) { wnb = yw * sx.n + xw + 1; wside = 0; }
     else { wnb = yw * sx.n + xw - 1; wside = 1; }
   }
+  // steps after which this node is no longer exact (its distance from the
+  // nearest cut side): it is left alone from then on
+  int far = nsteps;
+  if (sx.lo_cut) far = min(far, xw);
+  if (sx.hi_cut) far = min(far, sx.n - 1 - xw);
+  if (sy.lo_cut) far = min(far, yw);
+  if (sy.hi_cut) far = min(far, sy.n - 1 - yw);
+  __syncthreads();
   bool ok = true;
-  int P = 0;
   for (int s = 1; s <= nsteps; ++s) {
-    const int Q = P ^ 1;
-    if (active && !wall) {
-      double f[16], fxp[16], fxm[16], fyp[16], fym[16];
-      const int k0 = yw * sx.n + xw;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) f[i] = buf[P][i][k0];
-      NbrVel nv;
-      point(P, lxp, yw, nxp, cy, fxp, nv.ux_xp, nv.uy_xp);
-      point(P, lxm, yw, nxm, cy, fxm, nv.ux_xm, nv.uy_xm);
-      point(P, xw, lyp, cx, nyp, fyp, nv.ux_yp, nv.uy_yp);
-      point(P, xw, lym, cx, nym, fym, nv.ux_ym, nv.uy_ym);
-      double out[16];
-      const bool exact = (!sx.lo_cut || xw >= s) && (!sx.hi_cut || xw < sx.n - s) && (!sy.lo_cut || yw >= s) &&
-                         (!sy.hi_cut || yw < sy.n - s);
-      ok &= node_update<VER>(c, f, fxp, fxm, fyp, fym, nv, out) || !exact;
-      put(Q, out);
+    const bool update = active && !wall && s <= far;
+    if (update) {
+      double uxp = buf[16][kxp], vxp = buf[17][kxp], uxm = buf[16][kxm], vxm = buf[17][kxm];
+      double uyp = buf[16][kyp], vyp = buf[17][kyp], uym = buf[16][kym], vym = buf[17][kym];
+      if (mirrors) {
+        uxp = (flags & 1) ? -uxp : uxp;
+        uxm = (flags & 2) ? -uxm : uxm;
+        vyp = (flags & 4) ? -vyp : vyp;
+        vym = (flags & 8) ? -vym : vym;
+      }
+      const double A = mad(uxp - uxm, c.inv2dx, -((vyp - vym) * c.inv2dy));
+      const double B = mad(vxp - vxm, c.inv2dx, (uyp - uym) * c.inv2dy);
+      double df[16];
+      ok &= collide_from_moments<VER>(c, m, ir, A, B, df);
+      if (mirrors)
+        window_convect<0, true, W>(c, buf, kxp, kxm, kyp, kym, flags, f, df);
+      else
+        window_convect<0, false, W>(c, buf, kxp, kxm, kyp, kym, flags, f, df);
+      moments_from_f(f, m);
+      ir = recip(m[0]);
     }
+    __syncthreads();  // every node of this step has been read
+    if (update) put(f, m[1] * ir, m[2] * ir);
     __syncthreads();
     if (WALLS) {
       if (wall) {
-        double fn[16], fw[16];
+        double fn[16];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) fn[i] = buf[Q][i][wnb];
-        neq_wall<VER>(cold->wall[wside], fn, fw);
-        put(Q, fw);
+        for (int i = 0; i < 16; ++i) fn[i] = buf[i][wnb];
+        neq_wall<VER>(cold->wall[wside], fn, f);
+        moments_from_f(f, m);
+        ir = recip(m[0]);
+        put(f, m[1] * ir, m[2] * ir);
       }
       __syncthreads();
     }
-    P = Q;
   }
   if (active && xv >= sx.o && xv < sx.o + sx.v && xv >= 0 && xv < F.nx && yv >= sy.o && yv < sy.o + sy.v &&
       yv >= 0 && yv < F.ny) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) F.fout[i * F.plane + (long long)yg * F.pitch + xg] = buf[P][i][t];
+    for (int i = 0; i < 16; ++i) F.fout[at + i * F.plane] = f[i];
   }
   if (!ok) flag[0] = 1;
 }

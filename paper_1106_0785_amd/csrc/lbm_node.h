@@ -46,8 +46,13 @@ LBM_HD void moments_from_f(const double* f, double* m) {
   const int ks[4] = {0, 3, 10, 11};
   const int kx[4] = {1, 6, 8, 14};
   const int ky[4] = {2, 7, 9, 15};
+  // the conserved ones summed as in density_momentum, so that a node's own
+  // velocity and the one its neighbours see agree bit by bit
+  m[0] = (sig[0] + sig[1]) + (sig[2] + sig[3]);
+  m[1] = mad(2.0, gx[2] + gx[3], gx[0] + gx[1]);
+  m[2] = mad(2.0, gy[2] + gy[3], gy[0] + gy[1]);
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
+  for (int r = 1; r < 4; ++r) {
     // (sums start from their first term: adding to a zero is an operation)
     double a = A_SIG[r][0] * sig[0], b = A_GX[r][0] * gx[0], c = A_GY[r][0] * gy[0];
 #pragma unroll
@@ -71,8 +76,8 @@ LBM_HD void density_momentum(const double* f, double& rho, double& jx, double& j
   double sig[4], gx[4], gy[4], q[4];
   shell_quantities(f, sig, gx, gy, q);
   rho = (sig[0] + sig[1]) + (sig[2] + sig[3]);
-  jx = (gx[0] + gx[1]) + 2.0 * (gx[2] + gx[3]);
-  jy = (gy[0] + gy[1]) + 2.0 * (gy[2] + gy[3]);
+  jx = mad(2.0, gx[2] + gx[3], gx[0] + gx[1]);
+  jy = mad(2.0, gy[2] + gy[3], gy[0] + gy[1]);
 }
 
 // f = M^-1 m for a full moment vector m (index k-1 holds moment k). The
