@@ -367,21 +367,23 @@ hipError_t launch_window(const Field& F, const Hot* c, const Cold* cold, int ver
 }
 
 // Tiles of four waves, two workgroups per CU: a step takes full rounds of 512
-// tiles and a last one, which costs half as much when its tiles have a CU
-// each (at most 256). The height (a multiple of 4, at most 64) of the least
-// total; the constants are the start-up of a tile in rows, with and without
-// a second workgroup on its CU. Measured per step: 16 rows (512 tiles) 32.6
-// us at 1000 x 500 with walls, 8 rows (1008 tiles) 34.0, 20 rows (400) 36.0;
-// the flux-limited scheme at 2048 x 512 with 32 rows (512) 79.5, 16 rows
-// 85.1, 36 rows 84.4, and at 1023 x 257 with 20 rows (208) 34.3, 4 rows
-// (1040) 39.0.
+// tiles and a last one, which is cheaper when its tiles have a CU each (at
+// most 256). The height (a multiple of 4, at most 64) of the least total;
+// the weights are a row and a tile's start in each kind of round, and what a
+// launch costs once, fitted to heights of 4 to 64 on 22 grids of 60 000 to
+// 1 500 000 nodes (the height taken is within 6 % of the best). Measured per
+// step: 16 rows (512 tiles) 32.6 us at 1000 x 500 with walls, 8 rows (1008
+// tiles) 34.0, 20 rows (400) 36.0; the flux-limited scheme at 2048 x 512 with
+// 32 rows (512) 79.5, 16 rows 85.1, 36 rows 84.4, and at 1023 x 257 with 12
+// rows (352) 32.6, 20 rows (208) 34.3, 4 rows (1040) 39.0.
 TileShape default_tile(int nx, int ny) {
   const long long strips = (nx + STRIP - 1) / STRIP;
   int best = WAVES;
   long long cost = -1;
   for (int rows = WAVES; rows <= 64; rows += WAVES) {
     const long long tiles = strips * ((ny + rows - 1) / rows), last = tiles % 512;
-    const long long t = (tiles / 512) * 2 * (rows + 6) + (last == 0 ? 0 : last <= 256 ? rows + 14 : 2 * (rows + 6));
+    const long long two = 30 * rows + 90, one = 21 * rows + 40;
+    const long long t = tiles / 512 * two + (last == 0 ? 0 : last <= 256 ? one : two) + 120;
     if (cost < 0 || t < cost) cost = t, best = rows;
   }
   return TileShape{best, WAVES, default_nt(nx, ny)};
