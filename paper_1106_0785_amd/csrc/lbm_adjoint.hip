@@ -248,7 +248,7 @@ lbm_status lbm_adjoint_backward(lbm_adjoint* a, const double* d_rho0, const doub
                     : (ver == 2 ? k_adj_step<2, false> : ver == 3 ? k_adj_step<3, false> : k_adj_step<1, false>);
   // the LDS-staged step: 64-column tiles of 4 waves (at least 4 rows each, so
   // there are no more tiles than the per-block partial slots)
-  auto kfused = ver == 2 ? k_adj_fused<2, 4, true> : ver == 3 ? k_adj_fused<3, 4, true> : k_adj_fused<1, 4, true>;
+  auto kfused = ver == 2 ? k_adj_fused<2, 4> : ver == 3 ? k_adj_fused<3, 4> : k_adj_fused<1, 4>;
   const MarchGeom ag = march_geom(a->p.nx, a->p.ny, TileShape{adjoint_rows(a->p.nx, a->p.ny), 4, 1});
   for (int k = L.K - 1; k >= 0; --k) {
     const int64_t n0 = (int64_t)k * L.C, n1 = std::min<int64_t>(n0 + L.C, a->nsteps);

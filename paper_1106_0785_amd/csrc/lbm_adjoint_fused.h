@@ -8,7 +8,11 @@
 // fixed state: lambda 0, dL/dA = dL/dB = 0 and the state's velocity), so
 // every lambda and record value is read from HBM about once per step. The
 // node's own f^n (and f^{n-1} for the next step's records) go straight to
-// the lane that needs them. The arithmetic is adj_node's, in the same order.
+// the lane that needs them. The arithmetic is k_adj_step's, in the same order.
+// Bound by memory at large grids: 576 bytes per node and step (lambda, f^n,
+// f^{n-1} and the records in; lambda and the records out) at 5.2 TB/s, 231 us
+// at 2048 x 1024 (270 with four forward-mode sweeps of the collision and an
+// LDS address per plane).
 #pragma once
 
 #include "lbm_adjoint_kernels.h"
@@ -19,7 +23,7 @@ constexpr int NA = 20;  // ring entry: 16 lambda planes + GA, GB, ux, uy
 constexpr int RA = STRIP + 2;
 
 // Ghost values of a ring entry read from stored node (sx, sy) (resolve):
-// lambda as lam_src / lam_plane transform it, the record as rec_point does.
+// lambda as lam_src / lam_planes transform it, the record as rec_point does.
 __device__ __forceinline__ void fix_ghost_adj(const Hot& c, const Cold* __restrict__ cold, const Src& sx,
                                               const Src& sy, double* l, double* r) {
   if (__builtin_expect(sx.side < 0 && sy.side < 0, 1)) return;
@@ -56,115 +60,63 @@ __device__ __forceinline__ void fix_ghost_adj(const Hot& c, const Cold* __restri
 }
 
 // Transposed convection and identity for velocity I at ring column c0, the
-// new lambda stored at once (adj_node's AdjOut with ring reads).
+// new lambda stored at once (convect_t with ring reads).
 template <int I>
 struct AdjOutRing {
-  __device__ __forceinline__ static void run(const Hot& c, const double (*r0)[RA], const double (*rp)[RA],
-                                             const double (*rm)[RA], int c0, bool zxl, bool zxh, bool zyl,
-                                             bool zyh, double* __restrict__ lo, long long plane, double* out) {
-    const double l = r0[I][c0];
+  __device__ __forceinline__ static void run(const Hot& c, const double* r0, const double* rp, const double* rm,
+                                             const double* zx, const double* zy, double* __restrict__ lo,
+                                             long long plane, double* out) {
+    const double l = r0[I * RA];
     double v = out[I];
-    if (VX[I] != 0) v += conv_t_axis(VX[I], c.lx, r0[I][c0 - 1], r0[I][c0 + 1], l, zxl, zxh);
-    if (VY[I] != 0) v += conv_t_axis(VY[I], c.ly, rm[I][c0], rp[I][c0], l, zyl, zyh);
+    if constexpr (VX[I] != 0) v = conv_t_axis<VX[I]>(v, c.lx, zx, r0[I * RA - 1], r0[I * RA + 1], l);
+    if constexpr (VY[I] != 0) v = conv_t_axis<VY[I]>(v, c.ly, zy, rm[I * RA], rp[I * RA], l);
     out[I] = l + v;
     lo[I * plane] = out[I];
-    AdjOutRing<I + 1>::run(c, r0, rp, rm, c0, zxl, zxh, zyl, zyh, lo, plane, out);
+    AdjOutRing<I + 1>::run(c, r0, rp, rm, zx, zy, lo, plane, out);
   }
 };
 template <>
 struct AdjOutRing<16> {
-  __device__ __forceinline__ static void run(const Hot&, const double (*)[RA], const double (*)[RA],
-                                             const double (*)[RA], int, bool, bool, bool, bool, double* __restrict__,
-                                             long long, double*) {}
+  __device__ __forceinline__ static void run(const Hot&, const double*, const double*, const double*, const double*,
+                                             const double*, double* __restrict__, long long, double*) {}
 };
 
-// adj_node with lambda and the records of the node and its four neighbours
-// from ring rows r0 (the node's), rp (y+1), rm (y-1) at column c0; f is the
+// k_adj_step's node with lambda and the records of the node and its four neighbours
+// from ring rows r0 (the node's), rp (y+1), rm (y-1), each at the node's column; f is the
 // node's f^n. Writes lambda^n through lo (the node's address in lam_out) and,
 // when fp (the node's address in f^{n-1}) is given, the next step's record
 // of the node through ro.
-template <int VER, bool SERIAL>
-__device__ __forceinline__ void adj_node_ring(const Hot& c, const AdjCoef* __restrict__ adj, const double (*r0)[RA],
-                                              const double (*rp)[RA], const double (*rm)[RA], int c0,
-                                              const double* f, bool zxl, bool zxh, bool zyl, bool zyh,
+template <int VER>
+__device__ __forceinline__ void adj_node_ring(const Hot& c, const AdjCoef* __restrict__ adj, const double* r0,
+                                              const double* rp, const double* rm, const double* f, const double* zx, const double* zy,
                                               double* __restrict__ lo, long long plane, const double* fp,
                                               double* __restrict__ ro, double* sg) {
   double m[16];
   moments_from_f(f, m);
-  const double rho = m[0], ir = 1.0 / rho;
-  const double ux = m[1] * ir, uy = m[2] * ir;
-  const double T = m[3] * ir - 0.5 * (ux * ux + uy * uy);
-  const double rT = rho * T;
-  const double GAxp = r0[16 + REC_GA][c0 + 1], GBxp = r0[16 + REC_GB][c0 + 1];
-  const double uxxp = r0[16 + REC_UX][c0 + 1], uyxp = r0[16 + REC_UY][c0 + 1];
-  const double GAxm = r0[16 + REC_GA][c0 - 1], GBxm = r0[16 + REC_GB][c0 - 1];
-  const double uxxm = r0[16 + REC_UX][c0 - 1], uyxm = r0[16 + REC_UY][c0 - 1];
-  const double GAyp = rp[16 + REC_GA][c0], GByp = rp[16 + REC_GB][c0];
-  const double uxyp = rp[16 + REC_UX][c0], uyyp = rp[16 + REC_UY][c0];
-  const double GAym = rm[16 + REC_GA][c0], GBym = rm[16 + REC_GB][c0];
-  const double uxym = rm[16 + REC_UX][c0], uyym = rm[16 + REC_UY][c0];
+  const double GAxp = r0[(16 + REC_GA) * RA + 1], GBxp = r0[(16 + REC_GB) * RA + 1];
+  const double uxxp = r0[(16 + REC_UX) * RA + 1], uyxp = r0[(16 + REC_UY) * RA + 1];
+  const double GAxm = r0[(16 + REC_GA) * RA - 1], GBxm = r0[(16 + REC_GB) * RA - 1];
+  const double uxxm = r0[(16 + REC_UX) * RA - 1], uyxm = r0[(16 + REC_UY) * RA - 1];
+  const double GAyp = rp[(16 + REC_GA) * RA], GByp = rp[(16 + REC_GB) * RA];
+  const double uxyp = rp[(16 + REC_UX) * RA], uyyp = rp[(16 + REC_UY) * RA];
+  const double GAym = rm[(16 + REC_GA) * RA], GBym = rm[(16 + REC_GB) * RA];
+  const double uxym = rm[(16 + REC_UX) * RA], uyym = rm[(16 + REC_UY) * RA];
   const double A = (uxxp - uxxm) * c.inv2dx - (uyyp - uyym) * c.inv2dy;
   const double B = (uyxp - uyxm) * c.inv2dx + (uxyp - uxym) * c.inv2dy;
-  double mu[16];
+  const double gux = (GAxm - GAxp) * c.inv2dx + (GBym - GByp) * c.inv2dy;
+  const double guy = (GBxm - GBxp) * c.inv2dx - (GAym - GAyp) * c.inv2dy;
+  double mu[16], nu[16];
   {
     double l[16];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) l[i] = r0[i][c0];
+    for (int i = 0; i < 16; ++i) l[i] = r0[i * RA];
     minvt_apply(l, mu);
   }
-  {
-    double q[16];
-    equilibrium_moments<VER, double>(m[0], m[1], m[2], m[3], q);
-#pragma unroll
-    for (int k = 4; k < 16; ++k) sg[k - 4] += mu[k] * adj->mdt * (m[k] - q[k]);
-    const double a7 = rT * ux * A, b7 = rT * uy * B, b8 = rT * ux * B, a8 = rT * uy * A;
-    sg[0] += mu[6] * adj->dcm[0] * a7 + mu[7] * adj->dcm[6] * a8;
-    sg[1] += mu[6] * adj->dcm[2] * b7 + mu[7] * adj->dcm[4] * b8;
-    sg[2] += mu[6] * (adj->dcm[1] * a7 + adj->dcm[3] * b7);
-    sg[3] += mu[7] * (adj->dcm[5] * b8 + adj->dcm[7] * a8);
-  }
-  double nu[16];
-#pragma unroll
-  for (int k = 4; k < 16; ++k) nu[k] = c.cq[k - 4] * mu[k];
-  auto dual_dir = [&](int a) -> double {
-    Dual cc[4];
-#pragma unroll
-    for (int b = 0; b < 4; ++b) cc[b] = Dual(m[b], a == b ? 1.0 : 0.0);
-    Dual qd[16];
-    equilibrium_moments<VER, Dual>(cc[0], cc[1], cc[2], cc[3], qd);
-    double s = 0.0;
-#pragma unroll
-    for (int k = 4; k < 16; ++k) s -= nu[k] * qd[k].d;
-    const Dual iR = 1.0 / cc[0];
-    const Dual vxd = cc[1] * iR, vyd = cc[2] * iR;
-    const Dual Td = cc[3] * iR - 0.5 * (vxd * vxd + vyd * vyd);
-    const Dual rTd = cc[0] * Td;
-    const Dual g7 = c.cmod[0] * rTd * vxd * A + c.cmod[1] * rTd * vyd * B;
-    const Dual g8 = c.cmod[2] * rTd * vxd * B + c.cmod[3] * rTd * vyd * A;
-    return s + mu[6] * g7.d + mu[7] * g8.d;
-  };
-  double gc[4] = {0.0, 0.0, 0.0, 0.0};
-  if constexpr (SERIAL) {
-#pragma unroll 1
-    for (int a = 0; a < 4; ++a) {
-      const double g = dual_dir(a);
-#pragma unroll
-      for (int b = 0; b < 4; ++b) gc[b] = (a == b) ? g : gc[b];
-    }
-  } else {
-#pragma unroll
-    for (int a = 0; a < 4; ++a) gc[a] = dual_dir(a);
-  }
-  const double gux = (GAxm - GAxp) * c.inv2dx + (GBym - GByp) * c.inv2dy;
-  const double guy = (GBxm - GBxp) * c.inv2dx - (GAym - GAyp) * c.inv2dy;
-  gc[0] += -(ux * gux + uy * guy) * ir;
-  gc[1] += gux * ir;
-  gc[2] += guy * ir;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) nu[k] = gc[k];
+  collision_adjoint<VER>(c, adj, m, A, B, mu, gux, guy, nu, sg);
   double out[16];
   mt_apply(nu, out);
-  AdjOutRing<0>::run(c, r0, rp, rm, c0, zxl, zxh, zyl, zyh, lo, plane, out);
+  __builtin_amdgcn_sched_barrier(0);  // no ring reads before: they would take the collision's registers
+  AdjOutRing<0>::run(c, r0, rp, rm, zx, zy, lo, plane, out);
   if (fp) {
     double r[NREC], fq[16];
 #pragma unroll
@@ -179,7 +131,7 @@ __device__ __forceinline__ void adj_node_ring(const Hot& c, const AdjCoef* __res
 // the records of this step; lam_out = lambda^n; f_prev (may be NULL) =
 // f^{n-1}, whose records rec_out receives. The tile's dL/ds contribution
 // is added to partials[slot * 12 ..] (one slot per tile, fixed order).
-template <int VER, int W, bool SERIAL>
+template <int VER, int W>
 __device__ __forceinline__ void adj_tile(Field F, const double* __restrict__ lam_in, double* __restrict__ lam_out,
                                          const double* __restrict__ rec, const Hot* __restrict__ hot,
                                          const Cold* __restrict__ cold, const AdjCoef* __restrict__ adj,
@@ -266,6 +218,14 @@ __device__ __forceinline__ void adj_tile(Field F, const double* __restrict__ lam
     if (ewrite) ring[slot][eslot][ecol] = escale * ev + eoff;
   };
 
+  // the node's column of plane 0 in a ring row, its planes at constant offsets
+  // (opaque, or an address per plane is computed and kept for each)
+  auto at = [&](int slot) -> const double* {
+    int k = slot * (NA * RA) + c0;
+    asm volatile("" : "+v"(k));
+    return &ring[0][0][0] + k;
+  };
+
   // prologue: ring rows y0-1 .. y0+W (wave w fills slots w and w + W < RING)
   {
     double la[16], ra[NREC], lb[16], rb[NREC], ea, eb = 0.0;
@@ -279,6 +239,8 @@ __device__ __forceinline__ void adj_tile(Field F, const double* __restrict__ lam
 #pragma unroll
   for (int k = 0; k < 12; ++k) sg[k] = 0.0;
   const bool zxl = x == 0 && c.bc[0] == BC_ZERO_GRADIENT, zxh = x == nx - 1 && c.bc[1] == BC_ZERO_GRADIENT;
+  double zx[2];
+  zero_gradient_t(c.lx, zxl, zxh, zx);
   for (int Y = y0; Y < y1; Y += W) {
     const int y = Y + w;
     // the node's f^n, in flight across the barrier (the row entering the
@@ -292,10 +254,14 @@ __device__ __forceinline__ void adj_tile(Field F, const double* __restrict__ lam
       const int s0 = (unsigned)(y - base) % RING, sp = (unsigned)(y + 1 - base) % RING,
                 sm = (unsigned)(y - 1 - base) % RING;
       const bool zyl = y == 0 && c.bc[2] == BC_ZERO_GRADIENT, zyh = y == ny - 1 && c.bc[3] == BC_ZERO_GRADIENT;
-      adj_node_ring<VER, SERIAL>(c, adj, ring[s0], ring[sp], ring[sm], c0, f, zxl, zxh, zyl, zyh, lam_out + k0,
+      double zy[2];
+      zero_gradient_t(c.ly, zyl, zyh, zy);
+      adj_node_ring<VER>(c, adj, at(s0), at(sp), at(sm), f, zx, zy, lam_out + k0,
                                  F.plane, f_prev ? f_prev + k0 : nullptr, rec_out + k0, sg);
     }
-    // the row entering the ring after this iteration's updates
+    // the row entering the ring after this iteration's updates (not loaded
+    // earlier: that would take the update's registers)
+    __builtin_amdgcn_sched_barrier(0);
     const int yn = Y + W + 1 + w;
     double ln[16], rn[NREC], en;
     load_row(yn, ln, rn, en);
@@ -318,7 +284,7 @@ __device__ __forceinline__ void adj_tile(Field F, const double* __restrict__ lam
   }
 }
 
-template <int VER, int W, bool SERIAL>
+template <int VER, int W>
 __global__ __launch_bounds__(64 * W, 2) void k_adj_fused(Field F, const double* __restrict__ lam_in,
                                                         double* __restrict__ lam_out, const double* __restrict__ rec,
                                                         const Hot* __restrict__ hot, const Cold* __restrict__ cold,
@@ -327,7 +293,7 @@ __global__ __launch_bounds__(64 * W, 2) void k_adj_fused(Field F, const double* 
                                                         double* __restrict__ rec_out, MarchGeom g) {
   const int tile = xcd_tile(blockIdx.x, g);
   if (tile >= g.ntiles) return;  // whole workgroup leaves together
-  adj_tile<VER, W, SERIAL>(F, lam_in, lam_out, rec, hot, cold, adj, partials, f_prev, rec_out, g, tile);
+  adj_tile<VER, W>(F, lam_in, lam_out, rec, hot, cold, adj, partials, f_prev, rec_out, g, tile);
 }
 
 }  // namespace lbm

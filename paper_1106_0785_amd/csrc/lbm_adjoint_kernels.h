@@ -46,16 +46,13 @@ LBM_HD void record_from(const Hot& c, const double* f, const double* l, double* 
   double m[16], mu[16];
   moments_from_f(f, m);
   minvt_apply(l, mu);
-  const double rho = m[0], ir = 1.0 / rho;
+  const double ir = recip(m[0]);
   const double ux = m[1] * ir, uy = m[2] * ir;
-  const double T = m[3] * ir - 0.5 * (ux * ux + uy * uy);
-  const double rT = rho * T;
-  double vx, vy;
-  velocity_of(f, vx, vy);
+  const double rT = m[3] - 0.5 * (m[1] * ux + m[2] * uy);  // rho T
   r[REC_GA] = mu[6] * c.cmod[0] * rT * ux + mu[7] * c.cmod[3] * rT * uy;
   r[REC_GB] = mu[6] * c.cmod[1] * rT * uy + mu[7] * c.cmod[2] * rT * ux;
-  r[REC_UX] = vx;
-  r[REC_UY] = vy;
+  r[REC_UX] = ux;
+  r[REC_UY] = uy;
 }
 
 LBM_HD void adj_record(const Field& F, const Hot& c, const double* __restrict__ lam, double* __restrict__ rec, int x,
@@ -85,7 +82,8 @@ __global__ __launch_bounds__(256) void k_adj_records(Field F, const double* __re
 
 // Record of stencil point (x + ox, y + oy) of node (x, y) as its ghost
 // transposition requires; ux, uy are the velocity the forward step used.
-LBM_HD void rec_point(const Field& F, const Hot& c, const Cold* __restrict__ cold,
+template <class C>
+LBM_HD void rec_point(const Field& F, const C& c, const Cold* __restrict__ cold,
                                           const double* __restrict__ rec, int x, int y, int ox, int oy, double& GA,
                                           double& GB, double& ux, double& uy) {
   const int xn = x + ox, yn = y + oy;
@@ -107,191 +105,165 @@ LBM_HD void rec_point(const Field& F, const Hot& c, const Cold* __restrict__ col
   uy = fixed ? gy : (mirror && side >= 2) ? -vy : vy;
 }
 
-// Where the transposed convection finds lambda at stencil point (x + ox,
-// y + oy): the stored node k and how plane i maps onto it (0: plane i;
-// 1: mirror in x, mirrored plane; 3: mirror in y; 2: fixed-state ghost,
-// value 0; a zero-gradient ghost gives the node's own lambda and the caller
-// swaps the weights). Lets the caller load one plane at a time.
+// Lambda at a neighbour along one axis as the transposed convection takes it:
+// the stored node's address, the distance between a plane and the one it is
+// taken from in units of MIRROR[I] - I (the plane distance at a mirror ghost,
+// else 0), and whether it is a fixed-state ghost, which returns nothing. (A
+// zero-gradient ghost gives the node's own lambda and the caller corrects the
+// weights.)
 struct LamSrc {
-  long long k;
-  int mode;
+  const double* at;
+  long long d;
+  bool none;
 };
 
-LBM_HD LamSrc lam_src(const Field& F, const Hot& c, int x, int y, int ox, int oy) {
+template <class C>
+LBM_HD LamSrc lam_src(const Field& F, const C& c, const double* __restrict__ lam, int x, int y, int ox, int oy) {
   const Src sx = resolve(x + ox, F.nx, c.bc[0], c.bc[1], 0);
   const Src sy = resolve(y + oy, F.ny, c.bc[2], c.bc[3], 2);
   LamSrc r;
-  r.k = (long long)sy.idx * F.pitch + sx.idx;
-  r.mode = (sx.mode == 2 || sy.mode == 2) ? 2 : (sx.mode == 1 ? 1 : (sy.mode == 1 ? 3 : 0));
+  r.at = lam + ((long long)sy.idx * F.pitch + sx.idx);
+  r.d = (sx.mode == 1 || sy.mode == 1) ? F.plane : 0;
+  r.none = sx.mode == 2 || sy.mode == 2;
   return r;
 }
 
-// Plane I of lambda at a stencil point described by lam_src.
-template <int I>
-LBM_HD double lam_plane(const Field& F, const double* __restrict__ lam, LamSrc s) {
-  const int pl = (s.mode == 1) ? MIRROR_X[I] : ((s.mode == 3) ? MIRROR_Y[I] : I);
-  const double v = lam[s.k + (long long)pl * F.plane];
-  return (s.mode == 2) ? 0.0 : v;
+// The planes that move along the axis (0: x, 1: y) from the neighbour s.
+template <int AXIS, int I = 0>
+LBM_HD void lam_planes(const Field& F, const LamSrc& s, double* l) {
+  if constexpr ((AXIS == 0 ? VX[I] : VY[I]) != 0) {
+    constexpr int k = (AXIS == 0 ? MIRROR_X[I] : MIRROR_Y[I]) - I;
+    const double v = (s.at + k * s.d)[I * F.plane];
+    l[I] = s.none ? 0.0 : v;
+  }
+  if constexpr (I < 15) lam_planes<AXIS, I + 1>(F, s, l);
 }
 
-// Transposed Lax-Wendroff increment of velocity I along one axis; v is the
-// velocity component, (pm, mm) the weights as the forward step applies them
-// to (f(x+e) - f, f(x-e) - f), zl/zh true when the low/high neighbour is a
-// zero-gradient ghost.
-LBM_HD double conv_t_axis(int v, const double* lc, double lo, double hi, double lam, bool zl,
-                                              bool zh) {
-  // weights of f(x+e) (p) and f(x-e) (m) for this velocity
-  double p = 0.0, m = 0.0;
-  if (v == 1) { p = lc[0]; m = lc[1]; }
-  if (v == -1) { p = lc[1]; m = lc[0]; }
-  if (v == 2) { p = lc[2]; m = lc[3]; }
-  if (v == -2) { p = lc[3]; m = lc[2]; }
-  // node x is the + neighbour of x-e (weight p) and the - neighbour of x+e (weight m)
-  double r = p * (lo - lam) + m * (hi - lam);
-  if (zl) r += (m - p) * lam;  // ghost x-e = f(x): node x itself used weight m on it
-  if (zh) r += (p - m) * lam;  // ghost x+e = f(x): weight p
-  return r;
+// Transposed Lax-Wendroff increment of velocity component V along one axis,
+// added to r; lc as in Hot::lx, of which the forward step applies p to
+// (f(x+e) - f) and m to (f(x-e) - f). The node is the + neighbour of x-e
+// (weight p) and the - neighbour of x+e (weight m). cz corrects for
+// zero-gradient ghosts, which the node itself stands for: (m - p) of speeds 1
+// and 2 where the low neighbour is one, (p - m) where the high one is, else 0.
+template <int V>
+LBM_HD double conv_t_axis(double r, const double* lc, const double* cz, double lo, double hi, double lam) {
+  constexpr int a = V < 0 ? -V : V, p = 2 * (a - 1) + (V > 0 ? 0 : 1), m = 2 * (a - 1) + (V > 0 ? 1 : 0);
+  r = mad(lc[p], lo - lam, r);
+  r = mad(lc[m], hi - lam, r);
+  return mad(V > 0 ? cz[a - 1] : -cz[a - 1], lam, r);
 }
 
-// New adjoint lambda^n at node (x, y) into lam_out; adds this node's
-// contribution to dL/ds_5..16 (index k - 5) into sg.
-// With f_prev (the forward level of the next adjoint step, same layout as
-// F.fin) also writes that step's record of this node into rec_out.
-// Per-plane part of the transposed convection and identity for velocity I,
-// with the new lambda stored at once (so no neighbour plane set is kept).
-template <int I>
-struct AdjOut {
-  LBM_HD static void run(const Field& F, const Hot& c, const double* __restrict__ lam_in, double* __restrict__ lam_out,
-                         long long k0, LamSrc sxp, LamSrc sxm, LamSrc syp, LamSrc sym, bool zxl, bool zxh, bool zyl,
-                         bool zyh, double* out) {
-    const double l = lam_in[k0 + (long long)I * F.plane];
-    double v = out[I];
-    if (VX[I] != 0) v += conv_t_axis(VX[I], c.lx, lam_plane<I>(F, lam_in, sxm), lam_plane<I>(F, lam_in, sxp), l, zxl, zxh);
-    if (VY[I] != 0) v += conv_t_axis(VY[I], c.ly, lam_plane<I>(F, lam_in, sym), lam_plane<I>(F, lam_in, syp), l, zyl, zyh);
-    out[I] = l + v;
-    lam_out[k0 + (long long)I * F.plane] = out[I];
-    AdjOut<I + 1>::run(F, c, lam_in, lam_out, k0, sxp, sxm, syp, sym, zxl, zxh, zyl, zyh, out);
-  }
-};
-template <>
-struct AdjOut<16> {
-  LBM_HD static void run(const Field&, const Hot&, const double* __restrict__, double* __restrict__, long long, LamSrc,
-                         LamSrc, LamSrc, LamSrc, bool, bool, bool, bool, double*) {}
-};
+// cz of one axis (zl, zh: the node's low / high neighbour is a zero-gradient
+// ghost).
+LBM_HD void zero_gradient_t(const double* lc, bool zl, bool zh, double* cz) {
+  const double s = (zl ? 1.0 : 0.0) - (zh ? 1.0 : 0.0);
+  cz[0] = s * (lc[1] - lc[0]);
+  cz[1] = s * (lc[3] - lc[2]);
+}
 
-// New adjoint lambda^n at node (x, y) into lam_out; adds this node's
-// contribution to dL/ds_5..16 (index k - 5) into sg.
-// With f_prev (the forward level of the next adjoint step, same layout as
-// F.fin) also writes that step's record of this node into rec_out.
-// Ordered so that few values are live at once: the distributions are
-// dropped after their moments, dL/ds is formed as soon as mu is known, and
-// the transposed convection loads one plane of each neighbour at a time.
-template <int VER, bool SERIAL = false>
-LBM_HD void adj_node(const Field& F, const Hot& c, const Cold* __restrict__ cold, const AdjCoef* __restrict__ adj,
-                     const double* __restrict__ lam_in, double* __restrict__ lam_out, const double* __restrict__ rec,
-                     const double* __restrict__ f_prev, double* __restrict__ rec_out, int x, int y, double* sg) {
-  const long long k0 = (long long)y * F.pitch + x;
-  // --- forward quantities at the node
-  double m[16];
-  {
-    double f[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) f[i] = F.fin[k0 + i * F.plane];
-    moments_from_f(f, m);
-  }
-  const double rho = m[0], ir = 1.0 / rho;
-  const double ux = m[1] * ir, uy = m[2] * ir;
-  const double T = m[3] * ir - 0.5 * (ux * ux + uy * uy);
-  const double rT = rho * T;
-  // --- neighbour records: velocities for A, B and dL/dA, dL/dB
-  double GAxp, GBxp, uxxp, uyxp, GAxm, GBxm, uxxm, uyxm, GAyp, GByp, uxyp, uyyp, GAym, GBym, uxym, uyym;
-  rec_point(F, c, cold, rec, x, y, +1, 0, GAxp, GBxp, uxxp, uyxp);
-  rec_point(F, c, cold, rec, x, y, -1, 0, GAxm, GBxm, uxxm, uyxm);
-  rec_point(F, c, cold, rec, x, y, 0, +1, GAyp, GByp, uxyp, uyyp);
-  rec_point(F, c, cold, rec, x, y, 0, -1, GAym, GBym, uxym, uyym);
-  const double A = (uxxp - uxxm) * c.inv2dx - (uyyp - uyym) * c.inv2dy;
-  const double B = (uyxp - uyxm) * c.inv2dx + (uxyp - uxym) * c.inv2dy;
-  // --- collision adjoint
-  double mu[16];
-  {
-    double l[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) l[i] = lam_in[k0 + i * F.plane];
-    minvt_apply(l, mu);
-  }
-  // --- dL/ds: d col_k/d s_k = -dt (m_k - q_k), plus the modification's
+// Transposed convection of all velocities along one axis, added to out, from
+// lambda at the node (l) and at its two neighbours.
+template <int AXIS, int I = 0>
+LBM_HD void convect_t(const Hot& c, const double* cz, const double* l, const double* hi, const double* lo,
+                      double* out) {
+  constexpr int v = AXIS == 0 ? VX[I] : VY[I];
+  if constexpr (v != 0) out[I] = conv_t_axis<v>(out[I], AXIS == 0 ? c.lx : c.ly, cz, lo[I], hi[I], l[I]);
+  if constexpr (I < 15) convect_t<AXIS, I + 1>(c, cz, l, hi, lo, out);
+}
+
+// Adjoint of the collision at one node: from the moments m, the velocity
+// gradients A and B, mu = M^-T lambda and the neighbours' velocity terms
+// (gux, guy), the 16 moments nu whose M^T is the collision's part of the new
+// lambda: nu_k = -dt s_k mu_k for k >= 5 and, in the first four, dL/d(rho,
+// j_x, j_y, e) of the equilibria, the modification and the velocity. Adds the
+// node's dL/ds_5..16 to sg. The derivatives of the equilibria are taken in
+// reverse, one sweep over the forward intermediates (about 60 operations;
+// four forward-mode sweeps, one per conserved moment, took about 300).
+template <int VER>
+LBM_HD void collision_adjoint(const Hot& c, const AdjCoef* __restrict__ adj, const double* m, double A, double B,
+                              const double* mu, double gux, double guy, double* nu, double* sg) {
+  const double rho = m[0], jx = m[1], jy = m[2], e = m[3], ir = recip(rho);
+  const double ux = jx * ir, uy = jy * ir;
+  double q[16];
+  equilibrium_moments<VER, double>(rho, ir, jx, jy, e, q);
+  const double a = jx * ux, b = jy * uy, k = a + b;
+  const double rT = e - 0.5 * k;
+  // dL/ds: d col_k/d s_k = -dt (m_k - q_k), plus the modification's
   // coefficients (their s-derivatives already carry the factor dt)
-  {
-    double q[16];
-    equilibrium_moments<VER, double>(m[0], m[1], m[2], m[3], q);
 #pragma unroll
-    for (int k = 4; k < 16; ++k) sg[k - 4] = mu[k] * adj->mdt * (m[k] - q[k]);
-    const double a7 = rT * ux * A, b7 = rT * uy * B, b8 = rT * ux * B, a8 = rT * uy * A;
-    sg[0] += mu[6] * adj->dcm[0] * a7 + mu[7] * adj->dcm[6] * a8;   // s5
-    sg[1] += mu[6] * adj->dcm[2] * b7 + mu[7] * adj->dcm[4] * b8;   // s6
-    sg[2] += mu[6] * (adj->dcm[1] * a7 + adj->dcm[3] * b7);          // s7
-    sg[3] += mu[7] * (adj->dcm[5] * b8 + adj->dcm[7] * a8);          // s8
+  for (int i = 4; i < 16; ++i) sg[i - 4] += mu[i] * adj->mdt * (m[i] - q[i]);
+  const double tx = rT * ux, ty = rT * uy;
+  const double a7 = tx * A, b7 = ty * B, b8 = tx * B, a8 = ty * A;
+  sg[0] += mu[6] * adj->dcm[0] * a7 + mu[7] * adj->dcm[6] * a8;  // s5
+  sg[1] += mu[6] * adj->dcm[2] * b7 + mu[7] * adj->dcm[4] * b8;  // s6
+  sg[2] += mu[6] * (adj->dcm[1] * a7 + adj->dcm[3] * b7);        // s7
+  sg[3] += mu[7] * (adj->dcm[5] * b8 + adj->dcm[7] * a8);        // s8
+  double n[16];  // dL/dq_k = -nu_k
+#pragma unroll
+  for (int i = 4; i < 16; ++i) {
+    nu[i] = c.cq[i - 4] * mu[i];
+    n[i] = -nu[i];
   }
-  double nu[16];
+  // the intermediates of equilibrium_moments in reverse (g*: dL/d*)
+  const double ctx = mu[6] * c.cmod[0] * A + mu[7] * c.cmod[2] * B;  // dL/d(rho T u_x)
+  const double cty = mu[6] * c.cmod[1] * B + mu[7] * c.cmod[3] * A;
+  const double W = 6.0 * e - 2.0 * k;
+  const double gw = n[12] * q[4] + n[13] * q[5], gW = gw * ir;
+  const double gE = n[10] * ir;
+  double gir = n[10] * (2.0 * e * e - 0.25 * k * k) + gw * W;
+  const double g5 = n[4] + n[12] * (W * ir), g6 = n[5] + n[13] * (W * ir);
+  const double gh = n[6] * ux + n[7] * uy, h = e + rT;
+  const double h8 = n[8] * ux, h9 = n[9] * uy;
+  double gvx = gux + n[6] * h + n[8] * (a - 3.0 * b) + ctx * rT;
+  double gvy = guy + n[7] * h + n[9] * (3.0 * a - b) + cty * rT;
+  double grT = ctx * ux + cty * uy, grho = 0.0, gjx = 0.0, gjy = 0.0;
+  if constexpr (VER == 2) {
+    const double T = rT * ir, d = 5.0 * ux * ux - 5.0 * uy * uy;
+    gjx = n[14] * (-4.0 + 10.0 * T + d);
+    gjy = n[15] * (4.0 - 10.0 * T + d);
+    const double p = n[14] * jx, r = n[15] * jy;
+    const double gT = 10.0 * (p - r), gd = 10.0 * (p + r);
+    gvx += gd * ux;
+    gvy -= gd * uy;
+    grT += gT * ir;
+    gir += gT * rT;
+  } else if constexpr (VER == 3) {
+    // Maxwellian values fm_i weighted by M^T of the three moments taken of
+    // them: d fm / fm = drho/rho + c.du/T + (|c|^2/(2 T) - 1) dT/T, c = v - u
+    const double T = rT * ir, iT = 1.0 / T, pre = rho / (2.0 * M_PI * T), i2T = 0.5 / T;
+    double G0 = 0.0, Gx = 0.0, Gy = 0.0, G2 = 0.0;
 #pragma unroll
-  for (int k = 4; k < 16; ++k) nu[k] = c.cq[k - 4] * mu[k];
-  // conserved-moment adjoint: -J_q^T nu + mu7 dg7/dc + mu8 dg8/dc, by dual
-  // numbers, one derivative direction a at a time
-  auto dual_dir = [&](int a) -> double {
-    Dual cc[4];
-#pragma unroll
-    for (int b = 0; b < 4; ++b) cc[b] = Dual(m[b], a == b ? 1.0 : 0.0);
-    Dual qd[16];
-    equilibrium_moments<VER, Dual>(cc[0], cc[1], cc[2], cc[3], qd);
-    double s = 0.0;
-#pragma unroll
-    for (int k = 4; k < 16; ++k) s -= nu[k] * qd[k].d;
-    const Dual iR = 1.0 / cc[0];
-    const Dual vxd = cc[1] * iR, vyd = cc[2] * iR;
-    const Dual Td = cc[3] * iR - 0.5 * (vxd * vxd + vyd * vyd);
-    const Dual rTd = cc[0] * Td;
-    const Dual g7 = c.cmod[0] * rTd * vxd * A + c.cmod[1] * rTd * vyd * B;
-    const Dual g8 = c.cmod[2] * rTd * vxd * B + c.cmod[3] * rTd * vyd * A;
-    return s + mu[6] * g7.d + mu[7] * g8.d;
-  };
-  double gc[4] = {0.0, 0.0, 0.0, 0.0};
-  if constexpr (SERIAL) {
-    // not unrolled: interleaving the four evaluations would hold four times
-    // the registers (this form runs two blocks per CU)
-#pragma unroll 1
-    for (int a = 0; a < 4; ++a) {
-      const double g = dual_dir(a);
-#pragma unroll
-      for (int b = 0; b < 4; ++b) gc[b] = (a == b) ? g : gc[b];
+    for (int i = 0; i < 16; ++i) {
+      const int s = i / 4, p = i % 4;
+      const double sg3 = A_SIG[3][s] * n[11], gx3 = A_GX[3][s] * n[14], gy3 = A_GY[3][s] * n[15];
+      double w;
+      if (s == 0 || s == 2)
+        w = p == 0 ? sg3 + gx3 : p == 1 ? sg3 + gy3 : p == 2 ? sg3 - gx3 : sg3 - gy3;
+      else
+        w = p == 0 ? sg3 + (gx3 + gy3) : p == 1 ? sg3 - (gx3 - gy3) : p == 2 ? sg3 - (gx3 + gy3) : sg3 + (gx3 - gy3);
+      const double cx = (double)VX[i] - ux, cy = (double)VY[i] - uy, c2 = cx * cx + cy * cy;
+      const double v = w * (pre * sexp(-c2 * i2T));
+      G0 += v;
+      Gx += v * cx;
+      Gy += v * cy;
+      G2 += v * c2;
     }
-  } else {
-#pragma unroll
-    for (int a = 0; a < 4; ++a) gc[a] = dual_dir(a);
+    gvx += Gx * iT;
+    gvy += Gy * iT;
+    grho = G0 * ir;
+    const double gT = (G2 * i2T - G0) * iT;
+    grT += gT * ir;
+    gir += gT * rT;
   }
-  // velocity adjoint from the neighbours' gradient terms, then du/dc
-  const double gux = (GAxm - GAxp) * c.inv2dx + (GBym - GByp) * c.inv2dy;
-  const double guy = (GBxm - GBxp) * c.inv2dx - (GAym - GAyp) * c.inv2dy;
-  gc[0] += -(ux * gux + uy * guy) * ir;
-  gc[1] += gux * ir;
-  gc[2] += guy * ir;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) nu[k] = gc[k];
-  double out[16];
-  mt_apply(nu, out);
-  // --- transposed convection and identity, plane by plane
-  const LamSrc sxp = lam_src(F, c, x, y, +1, 0), sxm = lam_src(F, c, x, y, -1, 0);
-  const LamSrc syp = lam_src(F, c, x, y, 0, +1), sym = lam_src(F, c, x, y, 0, -1);
-  const bool zxl = x == 0 && c.bc[0] == BC_ZERO_GRADIENT, zxh = x == F.nx - 1 && c.bc[1] == BC_ZERO_GRADIENT;
-  const bool zyl = y == 0 && c.bc[2] == BC_ZERO_GRADIENT, zyh = y == F.ny - 1 && c.bc[3] == BC_ZERO_GRADIENT;
-  AdjOut<0>::run(F, c, lam_in, lam_out, k0, sxp, sxm, syp, sym, zxl, zxh, zyl, zyh, out);
-  if (f_prev) {
-    double fp[16], r[NREC];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) fp[i] = f_prev[k0 + i * F.plane];
-    record_from(c, fp, out, r);
-#pragma unroll
-    for (int j = 0; j < NREC; ++j) rec_out[k0 + j * F.plane] = r[j];
-  }
+  const double gk = -0.5 * (gh + grT) - 2.0 * gW - 0.5 * k * gE;
+  const double ga = gk + g5 + h8 + 3.0 * h9, gb = gk - g5 - 3.0 * h8 - h9;
+  gvx += ga * jx;
+  gvy += gb * jy + g6 * jx;
+  gir += gvx * jx + gvy * jy;
+  nu[0] = grho - (gir * ir) * ir;
+  nu[1] = gjx + ga * ux + g6 * uy + gvx * ir;
+  nu[2] = gjy + gb * uy + gvy * ir;
+  nu[3] = 2.0 * gh + grT + 6.0 * gW + 4.0 * e * gE;
 }
 
 // Value of lane l (uniform) of a wave.
@@ -309,29 +281,123 @@ __device__ __forceinline__ double wave_sum(double v) {
   return (read_lane(v, 0) + read_lane(v, 16)) + (read_lane(v, 32) + read_lane(v, 48));
 }
 
-// Launched with 64 x 4 threads per block. WIDE (large grids): two blocks per
-// CU, so that each SIMD has two waves to hide the latency of ~100 loads per
-// node (version 3 excepted: its Maxwellian terms would spill), at the cost of
-// evaluating the four dual directions one after another; otherwise one block
-// per CU with the four interleaved (small grids give each SIMD one wave
-// anyway, and then instruction-level parallelism is what hides latency).
+// New adjoint lambda^n of every node into lam_out, and the step's dL/ds_5..16
+// (index k - 5), one partial sum per block. With f_prev (the forward level of
+// the next adjoint step, same layout as F.fin) also writes that step's
+// records into rec_out. Launched with 64 x 4 threads per block.
+//
+// Bound by the latency of ~110 loads per node where a SIMD has one wave
+// (grids of up to 1024 waves), so they are issued as early as their addresses
+// are known: the node's own before the constants arrive, the neighbours'
+// before the collision, f_prev's without a branch, and all of them before the
+// first store (a wait for a later load would also wait for the stores before
+// it). WIDE (large grids): two blocks per CU, whose waves hide each other's
+// latency; the neighbours' planes are then loaded after the collision, which
+// keeps its registers free. 11.9 us at 512 x 128 (12.9 with each plane's loads
+// behind the previous plane's store, 12.6 with four forward-mode sweeps of
+// the collision).
 template <int VER, bool WIDE>
-__global__ __launch_bounds__(256, (WIDE && VER != 3) ? 2 : 1) void k_adj_step(Field F, const double* __restrict__ lam_in,
+__global__ __launch_bounds__(256, WIDE ? 2 : 1) void k_adj_step(Field F, const double* __restrict__ lam_in,
                                                   double* __restrict__ lam_out, const double* __restrict__ rec,
                                                   const Hot* __restrict__ hot, const Cold* __restrict__ cold,
                                                   const AdjCoef* __restrict__ adj, double* __restrict__ partials,
                                                   const double* __restrict__ f_prev, double* __restrict__ rec_out) {
   __shared__ Hot hs;
   __shared__ double red[12][4];
-  stage_hot(hot, &hs);
   const int t = threadIdx.y * blockDim.x + threadIdx.x;
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  const int y = blockIdx.y * blockDim.y + threadIdx.y;
-  double sg[12];
+  const int xt = blockIdx.x * blockDim.x + threadIdx.x, yt = blockIdx.y * blockDim.y + threadIdx.y;
+  const bool inside = xt < F.nx && yt < F.ny;
+  const int x = min(xt, F.nx - 1), y = min(yt, F.ny - 1);  // threads outside repeat an edge node
+  const long long k0 = (long long)y * F.pitch + x;
+  double f[16], l[16], fp[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) f[i] = F.fin[k0 + i * F.plane];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) l[i] = lam_in[k0 + i * F.plane];
+  const double* fpp = f_prev ? f_prev : F.fin;
+  auto load_prev = [&]() {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) fp[i] = fpp[k0 + i * F.plane];
+  };
+  if (!WIDE) load_prev();
+  // the block's running sum, added to at the end
+  const long long slot = (long long)blockIdx.y * gridDim.x + blockIdx.x;
+  const double psum = t < 12 ? partials[slot * 12 + t] : 0.0;
+  // the neighbours' addresses need the boundary kinds only, by scalar loads
+  struct {
+    int bc[4];
+  } side;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) side.bc[k] = __builtin_amdgcn_readfirstlane(hot->bc[k]);
+  const LamSrc sxp = lam_src(F, side, lam_in, x, y, +1, 0), sxm = lam_src(F, side, lam_in, x, y, -1, 0);
+  const LamSrc syp = lam_src(F, side, lam_in, x, y, 0, +1), sym = lam_src(F, side, lam_in, x, y, 0, -1);
+  double xp[16], xm[16], yp[16], ym[16];
+  auto load_x = [&]() {
+    lam_planes<0>(F, sxp, xp);
+    lam_planes<0>(F, sxm, xm);
+  };
+  auto load_y = [&]() {
+    lam_planes<1>(F, syp, yp);
+    lam_planes<1>(F, sym, ym);
+  };
+  if (!WIDE) {
+    load_x();
+    load_y();
+  }
+  // neighbour records: velocities for A, B and dL/dA, dL/dB
+  double GAxp, GBxp, uxxp, uyxp, GAxm, GBxm, uxxm, uyxm, GAyp, GByp, uxyp, uyyp, GAym, GBym, uxym, uyym;
+  rec_point(F, side, cold, rec, x, y, +1, 0, GAxp, GBxp, uxxp, uyxp);
+  rec_point(F, side, cold, rec, x, y, -1, 0, GAxm, GBxm, uxxm, uyxm);
+  rec_point(F, side, cold, rec, x, y, 0, +1, GAyp, GByp, uxyp, uyyp);
+  rec_point(F, side, cold, rec, x, y, 0, -1, GAym, GBym, uxym, uyym);
+  if (!WIDE) __builtin_amdgcn_sched_barrier(0);  // all issued by here, not one by one where they are used
+  stage_hot(hot, &hs);
+  const Hot& c = hs;
+  const double A = (uxxp - uxxm) * c.inv2dx - (uyyp - uyym) * c.inv2dy;
+  const double B = (uyxp - uyxm) * c.inv2dx + (uxyp - uxym) * c.inv2dy;
+  const double gux = (GAxm - GAxp) * c.inv2dx + (GBym - GByp) * c.inv2dy;
+  const double guy = (GBxm - GBxp) * c.inv2dx - (GAym - GAyp) * c.inv2dy;
+  double sg[12], m[16], mu[16], nu[16], out[16];
 #pragma unroll
   for (int k = 0; k < 12; ++k) sg[k] = 0.0;
-  if (x < F.nx && y < F.ny)
-    adj_node<VER, WIDE && VER != 3>(F, hs, cold, adj, lam_in, lam_out, rec, f_prev, rec_out, x, y, sg);
+  moments_from_f(f, m);
+  minvt_apply(l, mu);
+  if (WIDE) __builtin_amdgcn_sched_barrier(0);
+  collision_adjoint<VER>(c, adj, m, A, B, mu, gux, guy, nu, sg);
+  mt_apply(nu, out);
+  const bool zxl = x == 0 && side.bc[0] == BC_ZERO_GRADIENT, zxh = x == F.nx - 1 && side.bc[1] == BC_ZERO_GRADIENT;
+  const bool zyl = y == 0 && side.bc[2] == BC_ZERO_GRADIENT, zyh = y == F.ny - 1 && side.bc[3] == BC_ZERO_GRADIENT;
+  double zx[2], zy[2];
+  zero_gradient_t(c.lx, zxl, zxh, zx);
+  zero_gradient_t(c.ly, zyl, zyh, zy);
+  if (WIDE) {
+    __builtin_amdgcn_sched_barrier(0);
+    load_x();
+  }
+  convect_t<0>(c, zx, l, xp, xm, out);
+  if (WIDE) {
+    __builtin_amdgcn_sched_barrier(0);
+    load_y();
+  }
+  convect_t<1>(c, zy, l, yp, ym, out);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) out[i] += l[i];
+  if (WIDE) {
+    __builtin_amdgcn_sched_barrier(0);
+    load_prev();
+  }
+  double r[NREC];
+  record_from(c, fp, out, r);
+  // threads outside store the edge node's values again, the same bits (under a
+  // branch the loads would move into it, behind each other's waits)
+#pragma unroll
+  for (int i = 0; i < 16; ++i) lam_out[k0 + i * F.plane] = out[i];
+  if (f_prev) {
+#pragma unroll
+    for (int j = 0; j < NREC; ++j) rec_out[k0 + j * F.plane] = r[j];
+  }
+#pragma unroll
+  for (int k = 0; k < 12; ++k) sg[k] = inside ? sg[k] : 0.0;
   // deterministic block reduction, one slot per block, accumulated over steps
 #pragma unroll
   for (int k = 0; k < 12; ++k) {
@@ -339,10 +405,7 @@ __global__ __launch_bounds__(256, (WIDE && VER != 3) ? 2 : 1) void k_adj_step(Fi
     if ((t & 63) == 0) red[k][t >> 6] = w;
   }
   __syncthreads();
-  if (t < 12) {
-    const long long slot = (long long)blockIdx.y * gridDim.x + blockIdx.x;
-    partials[slot * 12 + t] += (red[t][0] + red[t][1]) + (red[t][2] + red[t][3]);
-  }
+  if (t < 12) partials[slot * 12 + t] = psum + ((red[t][0] + red[t][1]) + (red[t][2] + red[t][3]));
 }
 
 }  // namespace lbm
