@@ -74,6 +74,10 @@ struct lbm_adjoint {
   Consts host;
   AdjCoef adj;
   bool forward_done;
+  // Segment whose levels the segment store holds, -1 if none. Not kept once a
+  // call was captured into a graph: its replays overwrite the store unseen.
+  int held = -1;
+  bool captured = false;
   int variant;  // adjoint step: 0 LDS-staged tiles, 1 one thread per node, global gathers
   double* state(size_t off, int i) { return (double*)(base + off) + (size_t)i * 16 * L.plane; }
   double* ckpt(int k) { return state(L.ckpt, k); }
@@ -99,6 +103,17 @@ struct lbm_adjoint {
     return F;
   }
 };
+
+// Notes a stream capture; returns true when this handle has seen one.
+static bool capture_seen(lbm_adjoint* a) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(a->stream, &st) != hipSuccess) {
+    (void)hipGetLastError();  // not this call's error
+    a->captured = true;
+  }
+  if (st != hipStreamCaptureStatusNone) a->captured = true;
+  return a->captured;
+}
 
 static hipError_t step_into(lbm_adjoint* a, const double* fin, double* fout) {
   return launch_step(a->field(fin, fout), a->dhot(), a->dcold(), a->p.eq_version, has_walls(&a->p), 0, 0,
@@ -184,27 +199,47 @@ lbm_status lbm_adjoint_forward(lbm_adjoint* a, const double* d_rho0, const doubl
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "k_init launch");
   }
+  a->held = -1;
   const int C = a->L.C, K = a->L.K;
-  // between checkpoints no intermediate state is kept, so where the problem
-  // takes the two-step kernel by default, steps go two per launch
-  const bool two = default_variant(&a->p) == 4;
+  // between checkpoints no intermediate state is kept, so steps go many per
+  // launch with the kernel the problem takes by default (8.2 us per step one
+  // by one at 512 x 128, 7.0 in windows); the last segment's levels go one by
+  // one straight to where the backward pass reads them, which then need not
+  // recompute them
+  const int variant = default_variant(&a->p);
+  const bool walls = has_walls(&a->p);
   const TileShape t2 = default_tile2(a->p.nx, a->p.ny);
+  const WinGeom win = default_window(&a->p);
   for (int k = 0; k < K; ++k) {
     const int64_t n0 = (int64_t)k * C, n1 = std::min<int64_t>(n0 + C, a->nsteps);
     const double* fin = a->ckpt(k);
     int j = 0;
     for (int64_t n = n0; n < n1;) {
-      const int64_t take = (two && n1 - n >= 2) ? 2 : 1;
-      double* fout = (n + take == n1) ? a->ckpt(k + 1) : a->seg(j);
-      hipError_t e = take == 2 ? launch_step2(a->field(fin, fout), a->dhot(), a->dcold(), a->p.eq_version, t2,
-                                              a->flag(), a->stream)
-                               : step_into(a, fin, fout);
+      const int64_t left = n1 - n;
+      int64_t take = 1;
+      if (k < K - 1) {
+        if (variant == 2) take = std::min<int64_t>(1 << 16, left);
+        if (variant == 3) take = std::min<int64_t>(win.h, left);
+        if (variant == 4 && left >= 2) take = 2;
+      }
+      double* fout = n + take == n1 ? a->ckpt(k + 1) : a->seg(k < K - 1 ? j : (int)(n + take - n0));
+      const Field F = a->field(fin, fout);
+      hipError_t e;
+      if (take == 1)
+        e = step_into(a, fin, fout);
+      else if (variant == 2)
+        e = launch_small(F, a->dhot(), a->dcold(), ver, walls, (int)take, a->flag(), a->stream);
+      else if (variant == 3)
+        e = launch_window(F, a->dhot(), a->dcold(), ver, walls, win, (int)take, a->flag(), a->stream);
+      else
+        e = launch_step2(F, a->dhot(), a->dcold(), ver, t2, a->flag(), a->stream);
       if (e != hipSuccess) return hip_fail(e, "forward step launch");
       fin = fout;
       j ^= 1;
       n += take;
     }
   }
+  a->held = capture_seen(a) ? -1 : K - 1;
   a->forward_done = true;
   return LBM_OK;
 }
@@ -227,6 +262,7 @@ lbm_status lbm_adjoint_backward(lbm_adjoint* a, const double* d_rho0, const doub
                                 double* d_grad_ux0, double* d_grad_uy0, double* d_grad_T0, double* d_grad_s) {
   if (!a || !d_rho0 || !d_ux0 || !d_uy0 || !d_T0) return fail(LBM_EINVAL, "NULL argument");
   if (!a->forward_done) return fail(LBM_ESTATE, "run lbm_adjoint_forward first");
+  if (capture_seen(a)) a->held = -1;
   const int ver = a->p.eq_version;
   const AdjLayout& L = a->L;
   const dim3 grow((a->p.nx + 63) / 64, a->p.ny);
@@ -252,11 +288,16 @@ lbm_status lbm_adjoint_backward(lbm_adjoint* a, const double* d_rho0, const doub
   const MarchGeom ag = march_geom(a->p.nx, a->p.ny, TileShape{adjoint_rows(a->p.nx, a->p.ny), 4, 1});
   for (int k = L.K - 1; k >= 0; --k) {
     const int64_t n0 = (int64_t)k * L.C, n1 = std::min<int64_t>(n0 + L.C, a->nsteps);
-    // recompute f^{n0+1} .. f^{n1-1} into the segment store (f^{n0} is the checkpoint)
-    for (int64_t n = n0 + 1; n < n1; ++n) {
-      const double* fin = (n - 1 == n0) ? a->ckpt(k) : a->seg((int)(n - 1 - n0));
-      e = step_into(a, fin, a->seg((int)(n - n0)));
-      if (e != hipSuccess) return hip_fail(e, "recompute step launch");
+    // recompute f^{n0+1} .. f^{n1-1} into the segment store (f^{n0} is the
+    // checkpoint) unless it holds them already
+    if (a->held != k) {
+      a->held = -1;
+      for (int64_t n = n0 + 1; n < n1; ++n) {
+        const double* fin = (n - 1 == n0) ? a->ckpt(k) : a->seg((int)(n - 1 - n0));
+        e = step_into(a, fin, a->seg((int)(n - n0)));
+        if (e != hipSuccess) return hip_fail(e, "recompute step launch");
+      }
+      if (!a->captured) a->held = k;
     }
     // Each adjoint step n needs the records (dL/dA, dL/dB, velocity) of
     // every node at level n; step n writes those of step n - 1 as it
