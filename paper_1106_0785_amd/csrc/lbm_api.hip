@@ -254,18 +254,6 @@ bool small_problem(const lbm_params* p) {
   return p->scheme == 0 && (long long)p->nx * p->ny <= SMALL_NODES;
 }
 
-hipError_t launch_small(const Field& F, const Hot* c, const Cold* cold, int version, bool walls, int nsteps,
-                        int* flag, hipStream_t s) {
-  decltype(&k_step_small<1, false>) k;
-  if (walls)
-    k = version == 2 ? k_step_small<2, true> : version == 3 ? k_step_small<3, true> : k_step_small<1, true>;
-  else
-    k = version == 2 ? k_step_small<2, false> : version == 3 ? k_step_small<3, false> : k_step_small<1, false>;
-  const int threads = (F.nx * F.ny + 63) / 64 * 64;
-  hipLaunchKernelGGL(k, dim3(1), dim3(threads), 0, s, F, c, cold, nsteps, flag);
-  return hipGetLastError();
-}
-
 // True when the windowed kernel applies: scheme 0 and too big for the
 // small-grid kernel.
 bool window_problem(const lbm_params* p) { return p->scheme == 0 && !small_problem(p); }
@@ -361,10 +349,28 @@ hipError_t launch_window(const Field& F, const Hot* c, const Cold* cold, int ver
   } else {
     if (walls) LBM_WINDOW(true, SMALL_NODES); else LBM_WINDOW(false, SMALL_NODES);
   }
-#undef LBM_WINDOW
   hipLaunchKernelGGL(k, dim3(g.x.nwin * g.y.nwin), dim3(threads), 0, s, F, c, cold, g, nsteps, flag);
   return hipGetLastError();
 }
+
+// A small grid is one window that holds both axes whole; the instance of 512
+// nodes has the registers for one wave per SIMD.
+hipError_t launch_small(const Field& F, const Hot* c, const Cold* cold, int version, bool walls, int nsteps,
+                        int* flag, hipStream_t s) {
+  WinGeom g;
+  g.x = win_axis(F.nx, F.nx, 0, false);
+  g.y = win_axis(F.ny, F.ny, 0, false);
+  g.h = nsteps;
+  decltype(&k_step_window<1, false, SMALL_NODES>) k;
+  if (walls)
+    LBM_WINDOW(true, SMALL_NODES);
+  else
+    LBM_WINDOW(false, SMALL_NODES);
+  const int threads = (F.nx * F.ny + 63) / 64 * 64;
+  hipLaunchKernelGGL(k, dim3(1), dim3(threads), 0, s, F, c, cold, g, nsteps, flag);
+  return hipGetLastError();
+}
+#undef LBM_WINDOW
 
 // Tiles of four waves, two workgroups per CU: a step takes full rounds of 512
 // tiles and a last one, which is cheaper when its tiles have a CU each (at
