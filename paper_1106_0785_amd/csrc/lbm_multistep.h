@@ -154,40 +154,53 @@ __global__ __launch_bounds__(NODES, NODES <= 384 ? 3 : 2) void k_step_window(Fie
     ir = recip(m[0]);
     put(f, m[1] * ir, m[2] * ir);
   }
+  // A wall node's thread is a twin of its fluid neighbour: it updates the
+  // neighbour's state itself and takes the wall's from that, so walls need no
+  // phase of their own after the others' (one barrier and a pass through LDS
+  // less per step). (xu, yu): the node the thread updates, in the window.
+  const bool wall = WALLS && active && is_wall_node(c, xg, yg, F.nx, F.ny);
+  int xu = xw, yu = yw, wside = 0;
+  if (WALLS) {
+    const bool ylo = wall && c.bc[2] == BC_NEQ_WALL && yg == 0, yhi = wall && c.bc[3] == BC_NEQ_WALL && yg == F.ny - 1;
+    const bool xlo = wall && !ylo && !yhi && c.bc[0] == BC_NEQ_WALL && xg == 0, xhi = wall && !ylo && !yhi && !xlo;
+    wside = ylo ? 2 : yhi ? 3 : xlo ? 0 : 1;
+    yu += ylo ? 1 : yhi ? -1 : 0;
+    xu += xlo ? 1 : xhi ? -1 : 0;
+    if (active) {
+      const long long au = at + (long long)(yu - yw) * F.pitch + (xu - xw);
+#pragma unroll
+      for (int i = 0; i < 16; ++i) f[i] = F.fin[au + i * F.plane];
+      moments_from_f(f, m);
+      ir = recip(m[0]);
+    }
+  }
+  const int xgu = xg + (xu - xw), ygu = yg + (yu - yw);
   for (int k = t; k < 4 * NV; k += blockDim.x) {
     const int side = k / NV, i = k % NV;
     if (c.bc[side] == BC_DIRICHLET_EQ) buf[i][NODES + side] = i < 16 ? cold->ghost[side][i] : cold->gvel[side][i - 16];
   }
   int lxp, lxm, lyp, lym;
-  const Src nxp = win_nbr(sx, xw, xg, 1, F.nx, c.bc[0], c.bc[1], 0, lxp);
-  const Src nxm = win_nbr(sx, xw, xg, -1, F.nx, c.bc[0], c.bc[1], 0, lxm);
-  const Src nyp = win_nbr(sy, yw, yg, 1, F.ny, c.bc[2], c.bc[3], 2, lyp);
-  const Src nym = win_nbr(sy, yw, yg, -1, F.ny, c.bc[2], c.bc[3], 2, lym);
-  const int kxp = nxp.mode == 2 ? NODES + nxp.side : yw * sx.n + lxp;
-  const int kxm = nxm.mode == 2 ? NODES + nxm.side : yw * sx.n + lxm;
-  const int kyp = nyp.mode == 2 ? NODES + nyp.side : lyp * sx.n + xw;
-  const int kym = nym.mode == 2 ? NODES + nym.side : lym * sx.n + xw;
+  const Src nxp = win_nbr(sx, xu, xgu, 1, F.nx, c.bc[0], c.bc[1], 0, lxp);
+  const Src nxm = win_nbr(sx, xu, xgu, -1, F.nx, c.bc[0], c.bc[1], 0, lxm);
+  const Src nyp = win_nbr(sy, yu, ygu, 1, F.ny, c.bc[2], c.bc[3], 2, lyp);
+  const Src nym = win_nbr(sy, yu, ygu, -1, F.ny, c.bc[2], c.bc[3], 2, lym);
+  const int kxp = nxp.mode == 2 ? NODES + nxp.side : yu * sx.n + lxp;
+  const int kxm = nxm.mode == 2 ? NODES + nxm.side : yu * sx.n + lxm;
+  const int kyp = nyp.mode == 2 ? NODES + nyp.side : lyp * sx.n + xu;
+  const int kym = nym.mode == 2 ? NODES + nym.side : lym * sx.n + xu;
   const int flags = (nxp.mode == 1 ? 1 : 0) | (nxm.mode == 1 ? 2 : 0) | (nyp.mode == 1 ? 4 : 0) | (nym.mode == 1 ? 8 : 0);
   const bool mirrors = __any(flags != 0);  // wave-uniform
-  const bool wall = WALLS && active && is_wall_node(c, xg, yg, F.nx, F.ny);
-  int wnb = 0, wside = 0;
-  if (WALLS && wall) {
-    if (c.bc[2] == BC_NEQ_WALL && yg == 0) { wnb = (yw + 1) * sx.n + xw; wside = 2; }
-    else if (c.bc[3] == BC_NEQ_WALL && yg == F.ny - 1) { wnb = (yw - 1) * sx.n + xw; wside = 3; }
-    else if (c.bc[0] == BC_NEQ_WALL && xg == 0) { wnb = yw * sx.n + xw + 1; wside = 0; }
-    else { wnb = yw * sx.n + xw - 1; wside = 1; }
-  }
   // steps after which this node is no longer exact (its distance from the
   // nearest cut side): it is left alone from then on
   int far = nsteps;
-  if (sx.lo_cut) far = min(far, xw);
-  if (sx.hi_cut) far = min(far, sx.n - 1 - xw);
-  if (sy.lo_cut) far = min(far, yw);
-  if (sy.hi_cut) far = min(far, sy.n - 1 - yw);
+  if (sx.lo_cut) far = min(far, xu);
+  if (sx.hi_cut) far = min(far, sx.n - 1 - xu);
+  if (sy.lo_cut) far = min(far, yu);
+  if (sy.hi_cut) far = min(far, sy.n - 1 - yu);
   __syncthreads();
   bool ok = true;
   for (int s = 1; s <= nsteps; ++s) {
-    const bool update = active && !wall && s <= far;
+    const bool update = active && s <= far;
     if (update) {
       double uxp = buf[16][kxp], vxp = buf[17][kxp], uxm = buf[16][kxm], vxm = buf[17][kxm];
       double uyp = buf[16][kyp], vyp = buf[17][kyp], uym = buf[16][kym], vym = buf[17][kym];
@@ -209,20 +222,18 @@ __global__ __launch_bounds__(NODES, NODES <= 384 ? 3 : 2) void k_step_window(Fie
       ir = recip(m[0]);
     }
     __syncthreads();  // every node of this step has been read
-    if (update) put(f, m[1] * ir, m[2] * ir);
-    __syncthreads();
-    if (WALLS) {
-      if (wall) {
-        double fn[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) fn[i] = buf[i][wnb];
-        neq_wall<VER>(cold->wall[wside], fn, f);
-        moments_from_f(f, m);
-        ir = recip(m[0]);
-        put(f, m[1] * ir, m[2] * ir);
-      }
-      __syncthreads();
+    if (update && !wall) put(f, m[1] * ir, m[2] * ir);
+    if (WALLS && update && wall) {
+      double fw[16], ux, uy;
+      neq_wall<VER>(cold->wall[wside], f, fw);
+      velocity_of(fw, ux, uy);
+      put(fw, ux, uy);
     }
+    __syncthreads();
+  }
+  if (WALLS && wall) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) f[i] = buf[i][t];
   }
   if (active && xv >= sx.o && xv < sx.o + sx.v && xv >= 0 && xv < F.nx && yv >= sy.o && yv < sy.o + sy.v &&
       yv >= 0 && yv < F.ny) {
