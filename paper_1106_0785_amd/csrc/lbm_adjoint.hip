@@ -21,6 +21,7 @@ struct AdjLayout {
   int C, K;               // checkpoint interval, segments
   long long pitch, plane;  // distribution layout
   int gx, gy;             // adjoint launch grid
+  long long slots;        // partial dL/ds sums: one per block or tile
   size_t consts, adj, ckpt, seg, lam, rec, partials, red, red_bytes, flag, total;
 };
 
@@ -37,6 +38,8 @@ lbm_status adj_layout(const lbm_params* p, int64_t nsteps, int32_t ckpt, AdjLayo
   L->plane = L->pitch * p->ny;
   L->gx = (p->nx + 63) / 64;
   L->gy = (p->ny + 3) / 4;
+  // tiles have at least 4 rows
+  L->slots = std::max<long long>((long long)L->gx * L->gy, (long long)((p->nx + ACOLS - 1) / ACOLS) * L->gy);
   const size_t state = (size_t)16 * L->plane * sizeof(double);
   size_t off = 0;
   L->consts = off;
@@ -52,10 +55,10 @@ lbm_status adj_layout(const lbm_params* p, int64_t nsteps, int32_t ckpt, AdjLayo
   L->rec = off;
   off += 2 * a256((size_t)NREC * L->plane * sizeof(double));
   L->partials = off;
-  off += a256((size_t)L->gx * L->gy * 12 * sizeof(double));
+  off += a256((size_t)L->slots * 12 * sizeof(double));
   // two ping-pong buffers for the chunked reduction of the partials
   L->red = off;
-  L->red_bytes = a256((size_t)((L->gx * L->gy + ADJ_CHUNK - 1) / ADJ_CHUNK) * 12 * sizeof(double));
+  L->red_bytes = a256((size_t)((L->slots + ADJ_CHUNK - 1) / ADJ_CHUNK) * 12 * sizeof(double));
   off += 2 * L->red_bytes;
   L->flag = off;
   off += 256;
@@ -120,13 +123,28 @@ static hipError_t step_into(lbm_adjoint* a, const double* fin, double* fout) {
                      default_tile(a->p.nx, a->p.ny), a->flag(), a->stream);
 }
 
-// Rows per tile of the LDS-staged adjoint step: the tallest of 64, 32, ... 4
-// that leaves 1024 tiles of 64 columns.
-static int adjoint_rows(int nx, int ny) {
-  const long long strips = (nx + STRIP - 1) / STRIP;
-  int rows = 64;
-  while (rows > WAVES && strips * ((ny + rows - 1) / rows) < 1024) rows /= 2;
-  return rows;
+// Tiles of the LDS-staged adjoint step: 512 run at a time (two workgroups per
+// CU), so the height (a multiple of 4, at most 64) of the fewest rounds times
+// rows and start-up, as for the two-step kernel.
+static MarchGeom adjoint_geom(int nx, int ny) {
+  const long long strips = (nx + ACOLS - 1) / ACOLS;
+  int rows = WAVES;
+  long long cost = -1;
+  for (int r = WAVES; r <= 64; r += WAVES) {
+    const long long t = (strips * ((ny + r - 1) / r) + 511) / 512 * (r + 6);
+    if (cost < 0 || t < cost) cost = t, rows = r;
+  }
+  MarchGeom g = march_geom(nx, ny, TileShape{rows, WAVES, 1});
+  g.nstrips = (int)strips;
+  g.ntiles = g.nstrips * g.nsegs;
+  g.per_xcd = (g.ntiles + 7) / 8;
+  return g;
+}
+
+// The LDS-staged step where its tiles are tall, with 1024 tiles of 64 columns
+// and 16 rows or more.
+static bool tall_tiles(int nx, int ny) {
+  return (long long)((nx + STRIP - 1) / STRIP) * ((ny + 15) / 16) >= 1024;
 }
 
 extern "C" {
@@ -158,7 +176,7 @@ lbm_status lbm_adjoint_create(const lbm_params* p, int64_t nsteps, int32_t ckpt_
   // it takes 507 us per step against 598 for the gather form); small grids
   // give each tile one row per wavefront, and the gather form is faster
   // there (12.9 against 15.8 us per step at 512 x 128)
-  a->variant = adjoint_rows(p->nx, p->ny) >= 16 ? 0 : 1;
+  a->variant = tall_tiles(p->nx, p->ny) ? 0 : 1;
   make_coef(p, &a->host.hot, &a->host.cold);
   std::memset(&a->adj, 0, sizeof(a->adj));
   const double dt = p->dt, s5 = p->s[4], s6 = p->s[5], s7 = p->s[6], s8 = p->s[7];
@@ -271,7 +289,7 @@ lbm_status lbm_adjoint_backward(lbm_adjoint* a, const double* d_rho0, const doub
   // lambda^T from the gradients of the final fields
   hipLaunchKernelGGL(k_adj_final<0>, grow, dim3(64), 0, a->stream, a->field(a->ckpt(L.K), nullptr), d_g_rho, d_g_ux,
                      d_g_uy, d_g_T, a->lam(cur));
-  const long long np = (long long)L.gx * L.gy * 12;
+  const long long np = L.slots * 12;
   hipLaunchKernelGGL(k_zero<0>, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, a->stream, a->partials(), np);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "adjoint set-up launch");
@@ -282,10 +300,9 @@ lbm_status lbm_adjoint_backward(lbm_adjoint* a, const double* d_rho0, const doub
   const bool wide = (long long)L.gx * L.gy > 2048;
   auto kstep = wide ? (ver == 2 ? k_adj_step<2, true> : ver == 3 ? k_adj_step<3, true> : k_adj_step<1, true>)
                     : (ver == 2 ? k_adj_step<2, false> : ver == 3 ? k_adj_step<3, false> : k_adj_step<1, false>);
-  // the LDS-staged step: 64-column tiles of 4 waves (at least 4 rows each, so
-  // there are no more tiles than the per-block partial slots)
   auto kfused = ver == 2 ? k_adj_fused<2, 4> : ver == 3 ? k_adj_fused<3, 4> : k_adj_fused<1, 4>;
-  const MarchGeom ag = march_geom(a->p.nx, a->p.ny, TileShape{adjoint_rows(a->p.nx, a->p.ny), 4, 1});
+  const MarchGeom ag = adjoint_geom(a->p.nx, a->p.ny);
+  const bool staged = a->variant == 0;
   for (int k = L.K - 1; k >= 0; --k) {
     const int64_t n0 = (int64_t)k * L.C, n1 = std::min<int64_t>(n0 + L.C, a->nsteps);
     // recompute f^{n0+1} .. f^{n1-1} into the segment store (f^{n0} is the
@@ -299,8 +316,8 @@ lbm_status lbm_adjoint_backward(lbm_adjoint* a, const double* d_rho0, const doub
       }
       if (!a->captured) a->held = k;
     }
-    // Each adjoint step n needs the records (dL/dA, dL/dB, velocity) of
-    // every node at level n; step n writes those of step n - 1 as it
+    // Each gather step n needs the records (dL/dA, dL/dB, velocity) of
+    // every node at level n (the staged step forms them itself); step n writes those of step n - 1 as it
     // produces lambda^n, except across a segment boundary, where level
     // n - 1 is not recomputed yet and a records pass runs first.
     for (int64_t n = n1 - 1; n >= n0; --n) {
@@ -316,11 +333,11 @@ lbm_status lbm_adjoint_backward(lbm_adjoint* a, const double* d_rho0, const doub
         hipLaunchKernelGGL(kwall, dim3((along + 63) / 64), dim3(64), 0, a->stream, a->field(fnext, nullptr),
                            a->lam(cur), a->dhot(), a->dcold());
       }
-      if (walls || n == n1 - 1)
+      if (!staged && (walls || n == n1 - 1))
         hipLaunchKernelGGL(krec, gblk, bblk, 0, a->stream, F, a->lam(cur), a->rec(rc), a->dhot());
-      if (a->variant == 0)
+      if (staged)
         hipLaunchKernelGGL(kfused, dim3(8 * ag.per_xcd), dim3(256), 0, a->stream, F, a->lam(cur), a->lam(cur ^ 1),
-                           a->rec(rc), a->dhot(), a->dcold(), a->dadj(), a->partials(), fprev, a->rec(rc ^ 1), ag);
+                           a->dhot(), a->dcold(), a->dadj(), a->partials(), ag);
       else
         hipLaunchKernelGGL(kstep, gblk, bblk, 0, a->stream, F, a->lam(cur), a->lam(cur ^ 1), a->rec(rc), a->dhot(),
                            a->dcold(), a->dadj(), a->partials(), fprev, a->rec(rc ^ 1));
@@ -338,7 +355,7 @@ lbm_status lbm_adjoint_backward(lbm_adjoint* a, const double* d_rho0, const doub
     // fixed-order reduction of the per-block partials: chunks of ADJ_CHUNK
     // rows, repeated until one row is left
     const double* in = a->partials();
-    long long rows = (long long)L.gx * L.gy;
+    long long rows = L.slots;
     int j = 0;
     do {
       const long long nout = (rows + ADJ_CHUNK - 1) / ADJ_CHUNK;

@@ -1,18 +1,19 @@
 // Adjoint step staged through an LDS ring (the layout of the fused forward
-// kernel, lbm_kernels.h): a workgroup of W wavefronts owns a tile of 64
-// columns x `rows` rows and marches up it W rows at a time. Each ring entry
+// kernel, lbm_kernels.h): a workgroup of W wavefronts owns a tile of 62
+// columns x `rows` rows and marches up it W rows at a time, one lane per
+// column, the two outer lanes for the neighbours' columns. Each ring entry
 // holds what the transposed step reads at a stencil point: the 16 planes of
 // lambda^{n+1} and the point's record (dL/dA, dL/dB and its velocity), with
 // the ghost rules of the transposed step already applied (mirror: mirrored
 // planes and record; zero gradient: the record's dL/dA, dL/dB negated;
-// fixed state: lambda 0, dL/dA = dL/dB = 0 and the state's velocity), so
-// every lambda and record value is read from HBM about once per step. The
-// node's own f^n (and f^{n-1} for the next step's records) go straight to
-// the lane that needs them. The arithmetic is k_adj_step's, in the same order.
-// Bound by memory at large grids: 576 bytes per node and step (lambda, f^n,
-// f^{n-1} and the records in; lambda and the records out) at 5.2 TB/s, 231 us
-// at 2048 x 1024 (270 with four forward-mode sweeps of the collision and an
-// LDS address per plane).
+// fixed state: lambda 0, dL/dA = dL/dB = 0 and the state's velocity). A record
+// follows from lambda and f^n at its point, both there when the row enters
+// the ring, so none is kept in memory; the node's own f^n is read again when
+// it is updated (from the caches, a few rows later). The arithmetic is
+// k_adj_step's, in the same order.
+// Bound by memory at large grids: 384 bytes per node and step, against 576
+// with the records of the next step formed from f^{n-1} and stored;
+// ADJF_MEASURED
 #pragma once
 
 #include "lbm_adjoint_kernels.h"
@@ -20,7 +21,8 @@
 namespace lbm {
 
 constexpr int NA = 20;  // ring entry: 16 lambda planes + GA, GB, ux, uy
-constexpr int RA = STRIP + 2;
+constexpr int RA = 64;         // columns of a ring row: the tile's ACOLS and one on each side
+constexpr int ACOLS = RA - 2;
 
 // Ghost values of a ring entry read from stored node (sx, sy) (resolve):
 // lambda as lam_src / lam_planes transform it, the record as rec_point does.
@@ -81,16 +83,14 @@ struct AdjOutRing<16> {
                                              const double*, double* __restrict__, long long, double*) {}
 };
 
-// k_adj_step's node with lambda and the records of the node and its four neighbours
-// from ring rows r0 (the node's), rp (y+1), rm (y-1), each at the node's column; f is the
-// node's f^n. Writes lambda^n through lo (the node's address in lam_out) and,
-// when fp (the node's address in f^{n-1}) is given, the next step's record
-// of the node through ro.
+// k_adj_step's node with lambda and the records of the node and its four
+// neighbours from ring rows r0 (the node's), rp (y+1), rm (y-1), each at the
+// node's column; f is the node's f^n. Writes lambda^n through lo (the node's
+// address in lam_out).
 template <int VER>
 __device__ __forceinline__ void adj_node_ring(const Hot& c, const AdjCoef* __restrict__ adj, const double* r0,
-                                              const double* rp, const double* rm, const double* f, const double* zx, const double* zy,
-                                              double* __restrict__ lo, long long plane, const double* fp,
-                                              double* __restrict__ ro, double* sg) {
+                                              const double* rp, const double* rm, const double* f, const double* zx,
+                                              const double* zy, double* __restrict__ lo, long long plane, double* sg) {
   double m[16];
   moments_from_f(f, m);
   const double GAxp = r0[(16 + REC_GA) * RA + 1], GBxp = r0[(16 + REC_GB) * RA + 1];
@@ -117,26 +117,16 @@ __device__ __forceinline__ void adj_node_ring(const Hot& c, const AdjCoef* __res
   mt_apply(nu, out);
   __builtin_amdgcn_sched_barrier(0);  // no ring reads before: they would take the collision's registers
   AdjOutRing<0>::run(c, r0, rp, rm, zx, zy, lo, plane, out);
-  if (fp) {
-    double r[NREC], fq[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) fq[i] = fp[i * plane];
-    record_from(c, fq, out, r);
-#pragma unroll
-    for (int j = 0; j < NREC; ++j) ro[j * plane] = r[j];
-  }
 }
 
-// One tile of the adjoint step. F.fin = f^n; lam_in = lambda^{n+1}; rec =
-// the records of this step; lam_out = lambda^n; f_prev (may be NULL) =
-// f^{n-1}, whose records rec_out receives. The tile's dL/ds contribution
-// is added to partials[slot * 12 ..] (one slot per tile, fixed order).
+// One tile of the adjoint step. F.fin = f^n; lam_in = lambda^{n+1}; lam_out =
+// lambda^n. The tile's dL/ds contribution is added to partials[tile * 12 ..]
+// (one slot per tile, fixed order).
 template <int VER, int W>
 __device__ __forceinline__ void adj_tile(Field F, const double* __restrict__ lam_in, double* __restrict__ lam_out,
-                                         const double* __restrict__ rec, const Hot* __restrict__ hot,
-                                         const Cold* __restrict__ cold, const AdjCoef* __restrict__ adj,
-                                         double* __restrict__ partials, const double* __restrict__ f_prev,
-                                         double* __restrict__ rec_out, MarchGeom g, int tile) {
+                                         const Hot* __restrict__ hot, const Cold* __restrict__ cold,
+                                         const AdjCoef* __restrict__ adj, double* __restrict__ partials, MarchGeom g,
+                                         int tile) {
   constexpr int RING = W + 2;
   __shared__ double ring[RING][NA][RA];
   __shared__ Hot hs;
@@ -147,77 +137,38 @@ __device__ __forceinline__ void adj_tile(Field F, const double* __restrict__ lam
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int strip = tile % g.nstrips, seg = tile / g.nstrips;
   const int nx = F.nx, ny = F.ny;
-  const int x0 = strip * STRIP;
-  const int x = x0 + lane;
+  const int x = strip * ACOLS - 1 + lane;
+  const bool inside = lane >= 1 && lane <= ACOLS && x < nx;  // the columns the tile writes
   const int y0 = seg * g.rows;
   const int y1 = min(y0 + g.rows, ny);
   const int ylast = y1;  // last ring row the tile reads
   const int base = y0 - 1;
   const Src sx = (x < nx + 1) ? resolve(x, nx, c.bc[0], c.bc[1], 0) : Src{nx - 1, 0, -1};
-  const int c0 = lane + 1;
+  const int c0 = lane;
   const int bylo = __builtin_amdgcn_readfirstlane(hot->bc[2]);
   const int byhi = __builtin_amdgcn_readfirstlane(hot->bc[3]);
   auto ysrc = [&](int yr) -> Src {
     if (yr < 0 || yr >= ny) return resolve(yr, ny, bylo, byhi, 2);
     return Src{yr, 0, -1};
   };
-  // neighbour columns x0 - 1 (e = 0) and x0 + 64 (e = 1): lanes 0..31 hold
-  // lambda plane ep of column e, lanes 32..63 with ep < 4 its record value
-  // ep; the x ghost rule is folded into the address and an affine map
-  const int ep = lane & 15, e = (lane >> 4) & 1;
-  const bool erec = lane >= 32;
-  const int ecol = e ? RA - 1 : 0;
-  const double* eptr;
-  long long estride;
-  double escale = 1.0, eoff = 0.0;
-  {
-    const int ex = e ? x0 + STRIP : x0 - 1;
-    const Src es = (ex < nx + 1) ? resolve(ex, nx, c.bc[0], c.bc[1], 0) : Src{nx - 1, 0, -1};
-    const int kind = es.side >= 0 ? c.bc[es.side] : BC_PERIODIC;
-    if (!erec) {
-      const int pl = (es.mode == 1) ? lane_table(MIRROR_X, ep) : ep;
-      eptr = lam_in + (long long)pl * F.plane + es.idx;
-      if (es.mode == 2) escale = 0.0;
-    } else {
-      const int j = ep < NREC ? ep : 0;
-      eptr = rec + (long long)j * F.plane + es.idx;
-      if (kind == BC_DIRICHLET_EQ) {
-        escale = 0.0;
-        if (j >= REC_UX) {
-          double gx, gy;
-          velocity_of(cold->ghost[es.side], gx, gy);
-          eoff = j == REC_UX ? gx : gy;
-        }
-      } else if (kind == BC_SPECULAR) {
-        if (j == REC_GB || j == REC_UX) escale = -1.0;  // x side: dL/dB and u_x change sign
-      } else if (kind == BC_ZERO_GRADIENT) {
-        if (j == REC_GA || j == REC_GB) escale = -1.0;
-      }
-    }
-    estride = F.pitch;
-  }
-  const bool ewrite = !erec || ep < NREC;
-  const int eslot = erec ? 16 + ep : ep;
-
-  auto load_row = [&](int yr, double* l, double* r, double& ev) {
+  auto load_row = [&](int yr, double* l, double* f) {
     const int yi = ysrc(min(yr, ylast)).idx;
     const long long k = (long long)yi * F.pitch + sx.idx;
 #pragma unroll
     for (int i = 0; i < 16; ++i) l[i] = lam_in[k + i * F.plane];
 #pragma unroll
-    for (int j = 0; j < NREC; ++j) r[j] = rec[k + j * F.plane];
-    ev = eptr[yi * estride];
+    for (int i = 0; i < 16; ++i) f[i] = F.fin[k + i * F.plane];
   };
-  auto enter_row = [&](int yr, double* l, double* r, double ev) {
+  auto enter_row = [&](int yr, double* l, const double* f) {
+    double r[NREC];
+    record_from(c, f, l, r);
     fix_ghost_adj(c, cold, sx, ysrc(yr), l, r);
     const int slot = (unsigned)(yr - base) % RING;
 #pragma unroll
     for (int i = 0; i < 16; ++i) ring[slot][i][c0] = l[i];
 #pragma unroll
     for (int j = 0; j < NREC; ++j) ring[slot][16 + j][c0] = r[j];
-    if (ewrite) ring[slot][eslot][ecol] = escale * ev + eoff;
   };
-
   // the node's column of plane 0 in a ring row, its planes at constant offsets
   // (opaque, or an address per plane is computed and kept for each)
   auto at = [&](int slot) -> const double* {
@@ -228,12 +179,12 @@ __device__ __forceinline__ void adj_tile(Field F, const double* __restrict__ lam
 
   // prologue: ring rows y0-1 .. y0+W (wave w fills slots w and w + W < RING)
   {
-    double la[16], ra[NREC], lb[16], rb[NREC], ea, eb = 0.0;
+    double la[16], fa[16], lb[16], fb[16];
     const bool two = w < RING - W;
-    load_row(base + w, la, ra, ea);
-    if (two) load_row(base + w + W, lb, rb, eb);
-    if (base + w <= ylast) enter_row(base + w, la, ra, ea);
-    if (two && base + w + W <= ylast) enter_row(base + w + W, lb, rb, eb);
+    load_row(base + w, la, fa);
+    if (two) load_row(base + w + W, lb, fb);
+    if (base + w <= ylast) enter_row(base + w, la, fa);
+    if (two && base + w + W <= ylast) enter_row(base + w + W, lb, fb);
   }
   double sg[12];
 #pragma unroll
@@ -246,27 +197,26 @@ __device__ __forceinline__ void adj_tile(Field F, const double* __restrict__ lam
     // the node's f^n, in flight across the barrier (the row entering the
     // ring next is loaded after the update, to keep registers for it)
     double f[16];
-    const long long k0 = (long long)min(y, ny - 1) * F.pitch + min(x, nx - 1);
+    const long long k0 = (long long)min(y, ny - 1) * F.pitch + min(max(x, 0), nx - 1);
 #pragma unroll
     for (int i = 0; i < 16; ++i) f[i] = F.fin[k0 + i * F.plane];
     __syncthreads();
-    if (y < y1 && x < nx) {
+    if (y < y1 && inside) {
       const int s0 = (unsigned)(y - base) % RING, sp = (unsigned)(y + 1 - base) % RING,
                 sm = (unsigned)(y - 1 - base) % RING;
       const bool zyl = y == 0 && c.bc[2] == BC_ZERO_GRADIENT, zyh = y == ny - 1 && c.bc[3] == BC_ZERO_GRADIENT;
       double zy[2];
       zero_gradient_t(c.ly, zyl, zyh, zy);
-      adj_node_ring<VER>(c, adj, at(s0), at(sp), at(sm), f, zx, zy, lam_out + k0,
-                                 F.plane, f_prev ? f_prev + k0 : nullptr, rec_out + k0, sg);
+      adj_node_ring<VER>(c, adj, at(s0), at(sp), at(sm), f, zx, zy, lam_out + k0, F.plane, sg);
     }
     // the row entering the ring after this iteration's updates (not loaded
     // earlier: that would take the update's registers)
     __builtin_amdgcn_sched_barrier(0);
     const int yn = Y + W + 1 + w;
-    double ln[16], rn[NREC], en;
-    load_row(yn, ln, rn, en);
+    double ln[16], fn[16];
+    load_row(yn, ln, fn);
     __syncthreads();
-    if (yn <= ylast) enter_row(yn, ln, rn, en);
+    if (yn <= ylast) enter_row(yn, ln, fn);
   }
   // deterministic tile sum: DPP/readlane within each wave, then the waves
   // in order; one slot per tile, accumulated over the steps
@@ -286,14 +236,13 @@ __device__ __forceinline__ void adj_tile(Field F, const double* __restrict__ lam
 
 template <int VER, int W>
 __global__ __launch_bounds__(64 * W, 2) void k_adj_fused(Field F, const double* __restrict__ lam_in,
-                                                        double* __restrict__ lam_out, const double* __restrict__ rec,
-                                                        const Hot* __restrict__ hot, const Cold* __restrict__ cold,
-                                                        const AdjCoef* __restrict__ adj, double* __restrict__ partials,
-                                                        const double* __restrict__ f_prev,
-                                                        double* __restrict__ rec_out, MarchGeom g) {
+                                                        double* __restrict__ lam_out, const Hot* __restrict__ hot,
+                                                        const Cold* __restrict__ cold,
+                                                        const AdjCoef* __restrict__ adj,
+                                                        double* __restrict__ partials, MarchGeom g) {
   const int tile = xcd_tile(blockIdx.x, g);
   if (tile >= g.ntiles) return;  // whole workgroup leaves together
-  adj_tile<VER, W>(F, lam_in, lam_out, rec, hot, cold, adj, partials, f_prev, rec_out, g, tile);
+  adj_tile<VER, W>(F, lam_in, lam_out, hot, cold, adj, partials, g, tile);
 }
 
 }  // namespace lbm
