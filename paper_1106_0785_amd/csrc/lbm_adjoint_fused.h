@@ -8,12 +8,12 @@
 // planes and record; zero gradient: the record's dL/dA, dL/dB negated;
 // fixed state: lambda 0, dL/dA = dL/dB = 0 and the state's velocity). A record
 // follows from lambda and f^n at its point, both there when the row enters
-// the ring, so none is kept in memory; the node's own f^n is read again when
-// it is updated (from the caches, a few rows later). The arithmetic is
+// the ring, so none is kept in memory, and f^n stays with the wave that
+// updates the node (versions 1 and 2). The arithmetic is
 // k_adj_step's, in the same order.
 // Bound by memory at large grids: 384 bytes per node and step, against 576
 // with the records of the next step formed from f^{n-1} and stored;
-// ADJF_MEASURED
+// 202 us at 2048 x 1024 (231 so; 217 with f^n read again at the update).
 #pragma once
 
 #include "lbm_adjoint_kernels.h"
@@ -131,6 +131,7 @@ __device__ __forceinline__ void adj_tile(Field F, const double* __restrict__ lam
   __shared__ double ring[RING][NA][RA];
   __shared__ Hot hs;
   __shared__ double red[12][W];
+  __shared__ double held[16][RA];
   stage_hot(hot, &hs);
   const Hot& c = hs;
   const int lane = threadIdx.x & 63;
@@ -192,14 +193,31 @@ __device__ __forceinline__ void adj_tile(Field F, const double* __restrict__ lam
   const bool zxl = x == 0 && c.bc[0] == BC_ZERO_GRADIENT, zxh = x == nx - 1 && c.bc[1] == BC_ZERO_GRADIENT;
   double zx[2];
   zero_gradient_t(c.lx, zxl, zxh, zx);
+  // f^n of the row the wave updates next. Of the rows that enter the ring, a
+  // wave takes the one it updates in the next iteration (wave 0 the one after
+  // that, so it holds one row back), so f^n is read once. Version 3's update
+  // leaves no registers for that, nor for the row to be in flight during it:
+  // it reads f^n again.
+  constexpr bool KEEP = VER != 3;
+  double f[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) f[i] = F.fin[(long long)min(y0 + w, ny - 1) * F.pitch + sx.idx + i * F.plane];
+  if (KEEP && w == 0) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) held[i][lane] = F.fin[(long long)min(y0 + W, ny - 1) * F.pitch + sx.idx + i * F.plane];
+  }
   for (int Y = y0; Y < y1; Y += W) {
     const int y = Y + w;
-    // the node's f^n, in flight across the barrier (the row entering the
-    // ring next is loaded after the update, to keep registers for it)
-    double f[16];
     const long long k0 = (long long)min(y, ny - 1) * F.pitch + min(max(x, 0), nx - 1);
+    const int yn = w == 0 ? Y + 2 * W : Y + W + w;
+    double ln[16], fn[16];
+    if constexpr (KEEP) {
+      load_row(yn, ln, fn);  // in flight across the barrier
+    } else {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) f[i] = F.fin[k0 + i * F.plane];
+      for (int i = 0; i < 16; ++i) f[i] = F.fin[k0 + i * F.plane];
+    }
+    __builtin_amdgcn_sched_barrier(0);
     __syncthreads();
     if (y < y1 && inside) {
       const int s0 = (unsigned)(y - base) % RING, sp = (unsigned)(y + 1 - base) % RING,
@@ -209,14 +227,23 @@ __device__ __forceinline__ void adj_tile(Field F, const double* __restrict__ lam
       zero_gradient_t(c.ly, zyl, zyh, zy);
       adj_node_ring<VER>(c, adj, at(s0), at(sp), at(sm), f, zx, zy, lam_out + k0, F.plane, sg);
     }
-    // the row entering the ring after this iteration's updates (not loaded
-    // earlier: that would take the update's registers)
-    __builtin_amdgcn_sched_barrier(0);
-    const int yn = Y + W + 1 + w;
-    double ln[16], fn[16];
-    load_row(yn, ln, fn);
+    if constexpr (!KEEP) {
+      __builtin_amdgcn_sched_barrier(0);
+      load_row(yn, ln, fn);
+    }
     __syncthreads();
     if (yn <= ylast) enter_row(yn, ln, fn);
+    if (!KEEP) continue;
+    if (w == 0) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        f[i] = held[i][lane];
+        held[i][lane] = fn[i];
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) f[i] = fn[i];
+    }
   }
   // deterministic tile sum: DPP/readlane within each wave, then the waves
   // in order; one slot per tile, accumulated over the steps
