@@ -58,7 +58,7 @@ def time_steps(sim, steps, warmup):
     return start.elapsed_time(stop) / 1e3  # seconds
 
 
-VARIANT_KERNELS = {0: "k_step_fused", 1: "k_step_plain", 2: "k_step_small", 3: "k_step_window", 4: "k_step_fused2"}
+VARIANT_KERNELS = {0: "k_step_fused", 1: "k_step_plain", 2: "k_step_window", 3: "k_step_window", 4: "k_step_fused2"}
 
 
 def run_problem(p, fields, steps, warmup, rows=None, tune=False):

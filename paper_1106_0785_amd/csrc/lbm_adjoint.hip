@@ -141,10 +141,15 @@ static MarchGeom adjoint_geom(int nx, int ny) {
   return g;
 }
 
-// The LDS-staged step where its tiles are tall, with 1024 tiles of 64 columns
-// and 16 rows or more.
-static bool tall_tiles(int nx, int ny) {
-  return (long long)((nx + STRIP - 1) / STRIP) * ((ny + 15) / 16) >= 1024;
+// The gather step where its blocks have a CU each (13.8 us per step at
+// 512 x 128, the LDS-staged one 17.8), or two on half of them and the staged
+// step's tiles would be 8 rows tall (26.4 against 28.7 at 1000 x 128); the
+// staged step otherwise (18.1 against 21.9 at 400 x 200 with 4-row tiles, 27.4
+// against 34.9 at 700 x 220, 59 against 89 at 900 x 600, 230 against 336 at
+// 2048 x 1024).
+static bool staged_step(int nx, int ny) {
+  const long long blocks = (long long)((nx + 63) / 64) * ((ny + 3) / 4);
+  return blocks > 512 || (blocks > 256 && adjoint_geom(nx, ny).rows == WAVES);
 }
 
 extern "C" {
@@ -172,11 +177,7 @@ lbm_status lbm_adjoint_create(const lbm_params* p, int64_t nsteps, int32_t ckpt_
   a->stream = (hipStream_t)hip_stream;
   a->base = (char*)d_workspace;
   a->forward_done = false;
-  // the LDS-staged step where its tiles are tall (large grids: at 4096 x 1024
-  // it takes 507 us per step against 598 for the gather form); small grids
-  // give each tile one row per wavefront, and the gather form is faster
-  // there (12.9 against 15.8 us per step at 512 x 128)
-  a->variant = tall_tiles(p->nx, p->ny) ? 0 : 1;
+  a->variant = staged_step(p->nx, p->ny) ? 0 : 1;
   make_coef(p, &a->host.hot, &a->host.cold);
   std::memset(&a->adj, 0, sizeof(a->adj));
   const double dt = p->dt, s5 = p->s[4], s6 = p->s[5], s7 = p->s[6], s8 = p->s[7];

@@ -1,8 +1,7 @@
-// Multi-step kernels for grids that one launch per step leaves bound by
-// launch cost or latency: the small-grid kernel (the whole grid in one
-// workgroup's LDS) and the windowed kernel (overlapping LDS windows, several
-// steps per launch). Both use the plain kernel's stencil, ghost rules and
-// node arithmetic.
+// Multi-step kernel for grids that one launch per step leaves bound by
+// launch cost or latency: overlapping LDS windows, several steps per launch
+// (a small grid is one window, the whole of it). The plain kernel's stencil,
+// ghost rules and node arithmetic.
 #pragma once
 
 #include "lbm_kernels.h"

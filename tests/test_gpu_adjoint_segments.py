@@ -54,3 +54,28 @@ def test_segments(kind, nx, ny, steps, ckpt):
     assert torch.equal(first, second)
     adj.forward(dev["rho"], dev["ux"], dev["uy"], dev["T"])
     assert torch.equal(first, flat(adj.backward(g_rho=g, g_T=0.3 * g)))
+
+
+# either side of the lines between the gather and the LDS-staged step, whose
+# tiles are 4 rows tall in the second and 8 in the third
+@pytest.mark.parametrize("nx,ny", [(512, 128), (400, 200), (512, 256), (513, 257)])
+def test_both_steps_at_the_lines_of_their_rule(nx, ny):
+    import torch
+
+    from paper_1106_0785_amd.autograd import Adjoint
+
+    p, fl = _problem("rm", nx, ny)
+    dev = [torch.as_tensor(np.ascontiguousarray(fl[k]), device="cuda") for k in ("rho", "ux", "uy", "T")]
+    g = torch.cos(torch.arange(nx * ny, dtype=torch.float64, device="cuda")).reshape(ny, nx)
+    res = []
+    for variant in (None, 0, 1):
+        a = Adjoint(p, 5, 3)
+        if variant is not None:
+            a.set_variant(variant)
+        a.forward(*dev)
+        grads, gs = a.backward(g_rho=g)
+        res.append([t.clone() for t in grads] + [gs.clone()])
+        a.close()
+    for other in res[1:]:
+        for x, y in zip(res[0], other):
+            assert float((x - y).abs().max()) <= 1e-12 * float(y.abs().max())
