@@ -278,7 +278,8 @@ def bench_stability(n=512, squarings=48, reps=5, cpu_points=400):
     pts = len(params) * th_h.shape[0]
     flops = pts * squarings * STAB_FLOPS_PER_SQUARING
     out = {"sets": len(params), "points": pts, "squarings": squarings, "seconds": t, "points_per_s": pts / t,
-           "tflops": flops / t / 1e12, "mfma_fp64_frac": flops / t / 78.6e12,
+           # of 48 products per point; the powers that become rank one need fewer
+           "equivalent_tflops": flops / t / 1e12,
            "max_omega": [float(v) for v in r.max(dim=1).values.cpu()]}
     idx = np.random.default_rng(0).integers(0, th_h.shape[0], size=cpu_points // len(params))
     t0 = time.perf_counter()
