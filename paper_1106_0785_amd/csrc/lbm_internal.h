@@ -49,6 +49,7 @@ bool small_problem(const lbm_params* p);
 bool window_problem(const lbm_params* p);
 bool narrow_problem(const lbm_params* p);
 WinGeom default_window(const lbm_params* p);
+WinAxis win_axis(int len, int w, int h, bool walls);
 hipError_t launch_small(const Field& F, const Hot* c, const Cold* cold, int version, bool walls, int nsteps,
                         int* flag, hipStream_t s);
 hipError_t launch_window(const Field& F, const Hot* c, const Cold* cold, int version, bool walls,

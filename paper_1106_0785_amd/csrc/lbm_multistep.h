@@ -118,7 +118,9 @@ __device__ __forceinline__ void window_convect(const Hot& c, const double (*buf)
 // 60 x 40 with walls, 6.6 against 8.8 at 512 x 128 (both 16 x 16 nodes, 4
 // steps), 9.2 against 11.9 at 400 x 300 (16 x 16, 3 steps), 2.1 against 2.6
 // at 2000 x 4 (64 x 4, 8 steps).
-template <int VER, bool WALLS, int NODES>
+// LEVELS: every step's state is stored, that of step s at fout + (s - 1) 16
+// planes (the adjoint keeps them).
+template <int VER, bool WALLS, int NODES, bool LEVELS = false>
 __global__ __launch_bounds__(NODES, NODES <= 384 ? 3 : 2) void k_step_window(Field F, const Hot* __restrict__ hot,
                                                       const Cold* __restrict__ cold, WinGeom wg, int nsteps,
                                                       int* flag) {
@@ -197,6 +199,10 @@ __global__ __launch_bounds__(NODES, NODES <= 384 ? 3 : 2) void k_step_window(Fie
   if (sy.lo_cut) far = min(far, yu);
   if (sy.hi_cut) far = min(far, sy.n - 1 - yu);
   __syncthreads();
+  auto writes = [&]() {
+    return active && xv >= sx.o && xv < sx.o + sx.v && xv >= 0 && xv < F.nx && yv >= sy.o && yv < sy.o + sy.v &&
+           yv >= 0 && yv < F.ny;
+  };
   bool ok = true;
   for (int s = 1; s <= nsteps; ++s) {
     const bool update = active && s <= far;
@@ -228,14 +234,22 @@ __global__ __launch_bounds__(NODES, NODES <= 384 ? 3 : 2) void k_step_window(Fie
       velocity_of(fw, ux, uy);
       put(fw, ux, uy);
     }
+    if (LEVELS && writes()) {  // (a wall node's state is in its own entry only)
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        F.fout[(s - 1) * 16 * F.plane + at + i * F.plane] = (WALLS && wall) ? buf[i][t] : f[i];
+    }
     __syncthreads();
+  }
+  if (LEVELS) {
+    if (!ok) flag[0] = 1;
+    return;
   }
   if (WALLS && wall) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) f[i] = buf[i][t];
   }
-  if (active && xv >= sx.o && xv < sx.o + sx.v && xv >= 0 && xv < F.nx && yv >= sy.o && yv < sy.o + sy.v &&
-      yv >= 0 && yv < F.ny) {
+  if (writes()) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) F.fout[at + i * F.plane] = f[i];
   }
