@@ -62,7 +62,8 @@ lbm_status lbm_adjoint_set_variant(lbm_adjoint* a, int32_t variant);
 
 /* Synchronises the stream and reads the device health flag of every step
  * the forward and reverse sweeps ran since the last check (the checkpointed
- * forward steps and the recomputed segments): LBM_OK, or LBM_ENONFINITE if
+ * forward steps and the segments a reverse sweep went through, recomputed or
+ * found stored): LBM_OK, or LBM_ENONFINITE if
  * one of them produced rho <= 0, T <= 0 or a NaN (the gradients of such a
  * trajectory are meaningless); the flag is then cleared. */
 lbm_status lbm_adjoint_check(lbm_adjoint* a);

@@ -17,6 +17,8 @@ namespace {
 
 size_t a256(size_t x) { return (x + 255) / 256 * 256; }
 
+constexpr int HEALTH_WORDS = 64;  // int32 words of the flag block
+
 struct AdjLayout {
   int C, K;               // checkpoint interval, segments
   long long pitch, plane;  // distribution layout
@@ -61,7 +63,7 @@ lbm_status adj_layout(const lbm_params* p, int64_t nsteps, int32_t ckpt, AdjLayo
   L->red_bytes = a256((size_t)((L->slots + ADJ_CHUNK - 1) / ADJ_CHUNK) * 12 * sizeof(double));
   off += 2 * L->red_bytes;
   L->flag = off;
-  off += 256;
+  off += HEALTH_WORDS * sizeof(int);
   L->total = off;
   return LBM_OK;
 }
@@ -81,6 +83,12 @@ struct lbm_adjoint {
   // call was captured into a graph: its replays overwrite the store unseen.
   int held = -1;
   bool captured = false;
+  // Health words (int32 in the flag block): word 0 of every other step, words
+  // 1..63 of the segments whose levels are stored, one after the other, so
+  // that a sweep that finds its levels held reports what recomputing them
+  // would. held_bad: the segment now held was found bad by a check.
+  int word = 0;
+  bool held_bad = false;
   int variant;  // adjoint step: 0 LDS-staged tiles, 1 one thread per node, global gathers
   double* state(size_t off, int i) { return (double*)(base + off) + (size_t)i * 16 * L.plane; }
   double* ckpt(int k) { return state(L.ckpt, k); }
@@ -118,9 +126,16 @@ static bool capture_seen(lbm_adjoint* a) {
   return a->captured;
 }
 
-static hipError_t step_into(lbm_adjoint* a, const double* fin, double* fout) {
+static hipError_t step_into(lbm_adjoint* a, const double* fin, double* fout, int* flag) {
   return launch_step(a->field(fin, fout), a->dhot(), a->dcold(), a->p.eq_version, has_walls(&a->p), 0, 0,
-                     default_tile(a->p.nx, a->p.ny), a->flag(), a->stream);
+                     default_tile(a->p.nx, a->p.ny), flag, a->stream);
+}
+
+// The segment store is about to be filled anew: the health word of its steps.
+static void new_levels(lbm_adjoint* a) {
+  a->held = -1;
+  a->held_bad = false;
+  a->word = a->word % (HEALTH_WORDS - 1) + 1;
 }
 
 // Steps from f^n (fin) into the levels of the segment store from `level` on,
@@ -132,8 +147,9 @@ static hipError_t step_into(lbm_adjoint* a, const double* fin, double* fout) {
 static hipError_t levels_into(lbm_adjoint* a, const double* fin, int level, int64_t left, int* taken) {
   const int variant = default_variant(&a->p), ver = a->p.eq_version;
   double* fout = a->seg(level);
+  int* flag = a->flag() + a->word;
   *taken = 1;
-  if (variant != 2 && variant != 3) return step_into(a, fin, fout);
+  if (variant != 2 && variant != 3) return step_into(a, fin, fout, flag);
   WinGeom g;
   if (variant == 2) {
     g.x = win_axis(a->p.nx, a->p.nx, 0, false);
@@ -141,7 +157,7 @@ static hipError_t levels_into(lbm_adjoint* a, const double* fin, int level, int6
     g.h = (int)std::min<int64_t>(1 << 16, left);
   } else {
     g = default_window(&a->p);
-    if ((long long)g.x.nwin * g.y.nwin > 256) return step_into(a, fin, fout);
+    if ((long long)g.x.nwin * g.y.nwin > 256) return step_into(a, fin, fout, flag);
   }
   *taken = (int)std::min<int64_t>(g.h, left);
   const int threads = (g.x.w * g.y.w + 63) / 64 * 64;
@@ -156,7 +172,7 @@ static hipError_t levels_into(lbm_adjoint* a, const double* fin, int level, int6
   }
 #undef LBM_LEVELS
   hipLaunchKernelGGL(k, dim3(g.x.nwin * g.y.nwin), dim3(threads), 0, a->stream, a->field(fin, fout), a->dhot(),
-                     a->dcold(), g, *taken, a->flag());
+                     a->dcold(), g, *taken, flag);
   return hipGetLastError();
 }
 
@@ -232,7 +248,7 @@ lbm_status lbm_adjoint_create(const lbm_params* p, int64_t nsteps, int32_t ckpt_
   }
   hipError_t e = hipMemcpyAsync(a->base + L.consts, &a->host, sizeof(Consts), hipMemcpyHostToDevice, a->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(a->base + L.adj, &a->adj, sizeof(AdjCoef), hipMemcpyHostToDevice, a->stream);
-  if (e == hipSuccess) e = hipMemsetAsync(a->flag(), 0, 256, a->stream);
+  if (e == hipSuccess) e = hipMemsetAsync(a->flag(), 0, HEALTH_WORDS * sizeof(int), a->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(a->stream);
   if (e != hipSuccess) {
     delete a;
@@ -255,7 +271,7 @@ lbm_status lbm_adjoint_forward(lbm_adjoint* a, const double* d_rho0, const doubl
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "k_init launch");
   }
-  a->held = -1;
+  new_levels(a);
   const int C = a->L.C, K = a->L.K;
   // between checkpoints no intermediate state is kept, so steps go many per
   // launch with the kernel the problem takes by default (8.2 us per step one
@@ -291,7 +307,7 @@ lbm_status lbm_adjoint_forward(lbm_adjoint* a, const double* d_rho0, const doubl
       double* fout = n + take == n1 ? a->ckpt(k + 1) : a->seg(j);
       const Field F = a->field(fin, fout);
       if (take == 1)
-        e = step_into(a, fin, fout);
+        e = step_into(a, fin, fout, a->flag());
       else if (variant == 2)
         e = launch_small(F, a->dhot(), a->dcold(), ver, walls, (int)take, a->flag(), a->stream);
       else if (variant == 3)
@@ -355,7 +371,7 @@ lbm_status lbm_adjoint_backward(lbm_adjoint* a, const double* d_rho0, const doub
     // recompute f^{n0+1} .. f^{n1-1} into the segment store (f^{n0} is the
     // checkpoint) unless it holds them already
     if (a->held != k) {
-      a->held = -1;
+      new_levels(a);
       for (int64_t n = n0 + 1; n < n1;) {
         const double* fin = (n - 1 == n0) ? a->ckpt(k) : a->seg((int)(n - 1 - n0));
         int taken = 0;
@@ -364,6 +380,10 @@ lbm_status lbm_adjoint_backward(lbm_adjoint* a, const double* d_rho0, const doub
         n += taken;
       }
       if (!a->captured) a->held = k;
+    } else if (a->held_bad) {
+      hipLaunchKernelGGL(k_raise_flag<0>, dim3(1), dim3(64), 0, a->stream, a->flag());
+      e = hipGetLastError();
+      if (e != hipSuccess) return hip_fail(e, "health flag launch");
     }
     // Each gather step n needs the records (dL/dA, dL/dB, velocity) of
     // every node at level n (the staged step forms them itself); step n writes those of step n - 1 as it
@@ -430,12 +450,15 @@ lbm_status lbm_adjoint_set_variant(lbm_adjoint* a, int32_t variant) {
 
 lbm_status lbm_adjoint_check(lbm_adjoint* a) {
   if (!a) return fail(LBM_EINVAL, "adjoint handle is NULL");
-  int flag = 0;
-  hipError_t e = hipMemcpyAsync(&flag, a->flag(), sizeof(int), hipMemcpyDeviceToHost, a->stream);
+  int words[HEALTH_WORDS] = {};
+  hipError_t e = hipMemcpyAsync(words, a->flag(), sizeof(words), hipMemcpyDeviceToHost, a->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(a->stream);
   if (e != hipSuccess) return hip_fail(e, "reading the health flag");
-  if (flag) {
-    e = hipMemsetAsync(a->flag(), 0, sizeof(int), a->stream);
+  bool bad = false;
+  for (int v : words) bad |= v != 0;
+  if (bad) {
+    if (words[a->word] != 0) a->held_bad = true;
+    e = hipMemsetAsync(a->flag(), 0, sizeof(words), a->stream);
     if (e != hipSuccess) return hip_fail(e, "hipMemsetAsync");
     return fail(LBM_ENONFINITE, "a forward step produced rho <= 0, T <= 0 or NaN");
   }

@@ -594,6 +594,11 @@ __global__ void k_adj_grad(const double* __restrict__ row, double* __restrict__ 
 }
 
 template <int U>
+__global__ void k_raise_flag(int* flag) {
+  if (threadIdx.x == 0) flag[0] = 1;
+}
+
+template <int U>
 __global__ void k_zero(double* p, long long n) {
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0.0;
