@@ -34,6 +34,7 @@
 #include "lbm_internal.h"
 #include "lbm_kernels.h"
 #include "lbm_node.h"
+#include "lbm_rank_one.h"
 
 using namespace lbm;
 
@@ -179,20 +180,19 @@ __device__ __forceinline__ double wave_max(double v) {
 // X^(2^k) = mu^(2^k - 1) X, and the squarings left have a closed form:
 //   log2 |omega| += log2 |mu| (2^-(j-1) - 2^-squarings)   for X at level j - 1.
 // X^2 = mu X is taken to hold when the largest entry of X^2 - mu X has been
-// below RANK_TOL |mu| max|X| at two squarings in a row: the first says that
-// what the other eigenvalues leave in X is below 2^-46, the second has
-// squared that, so all that is left there is the rounding of one product,
+// below RANK_TOL |mu| |o| (o: the entry of X that was its largest at the last
+// rescaling) at two squarings in a row: the first says that what the other
+// eigenvalues leave in X is below 2^-44, the second has squared that, so all that is left there is the rounding of one product,
 // which every squaring commits and which enters with its level's weight
-// 2^-j: from level CLOSE_FROM on, 64 units of it weigh less than an eighth of
-// the first squaring's own. Powers that stay off rank one (eigenvalues of
+// 2^-j: from level CLOSE_FROM on, 256 units of it weigh a sixteenth of the
+// first squaring's own. Powers that stay off rank one (eigenvalues of
 // equal modulus) are squared to the end. Fig. 2 maps: rank one after 13-21 of
 // the 48 squarings at nine points in ten.
 // The largest component of X^(2^k) depends on the phase of mu^(2^k), which
 // the closed form leaves out: at most 2^-(squarings + 1) in log2 |omega|, so
 // only calls of at least CLOSE_SQUARINGS squarings (the default's) use it.
-constexpr double RANK_TOL = 0x1p-46;
 constexpr int CLOSE_SQUARINGS = 48;
-constexpr int CLOSE_FROM = 10;
+constexpr int CLOSE_FROM = 12;
 // Squarings between rescalings (and between comparisons): components stay
 // below 2^20 and far from underflow over two, and the scale is exact, so the
 // search for the largest component is not needed at each (with the search by
@@ -248,20 +248,16 @@ __global__ __launch_bounds__(64, 4) void k_stab_radius(const StabCoef* __restric
         }
         __syncthreads();  // every lane has read X before the next write
         if (squarings >= CLOSE_SQUARINGS && j >= CLOSE_FROM && (close || j % RESCALE == 0)) {
-          // mu = n / o from X's entry o that was the largest at the last
-          // rescaling; both sides times |o|^2
+          // o: X's entry that was the largest at the last rescaling
           const double ore = from_lane(pick(xr, top), top_lane), oim = from_lane(pick(xi, top), top_lane);
           const double nre = from_lane(pick(ar4, top), top_lane), nim = from_lane(pick(ai4, top), top_lane);
-          const double o2 = ore * ore + oim * oim, n2 = nre * nre + nim * nim;
-          const double mr = nre * ore + nim * oim, mi = nim * ore - nre * oim;
+          const RankOne ro = rank_one(ore, oim, nre, nim);
           double d = 0.0;
 #pragma unroll
-          for (int r = 0; r < 4; ++r)
-            d = fmax(d, fmax(fabs(o2 * ar4[r] - (mr * xr[r] - mi * xi[r])),
-                             fabs(o2 * ai4[r] - (mr * xi[r] + mi * xr[r]))));
-          if (__all(d * d < RANK_TOL * RANK_TOL * n2 * o2)) {
+          for (int r = 0; r < 4; ++r) d = fmax(d, rank_one_gap(ro, xr[r], xi[r], ar4[r], ai4[r]));
+          if (__all(rank_one_within(ro, d))) {
             if (close) {
-              L += 0.5 * log2(n2 / o2) * (ldexp(1.0, 1 - j) - ldexp(1.0, -squarings));
+              L += 0.5 * log2(ro.n2 / ro.o2) * (ldexp(1.0, 1 - j) - ldexp(1.0, -squarings));
               frac = fmax(fabs(ore), fabs(oim));
               break;
             }
