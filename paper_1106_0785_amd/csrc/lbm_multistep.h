@@ -204,7 +204,7 @@ __global__ __launch_bounds__(NODES, NODES <= 384 ? 3 : 2) void k_step_window(Fie
            yv >= 0 && yv < F.ny;
   };
   bool ok = true;
-  for (int s = 1; s <= nsteps; ++s) {
+  for (int s = 1;; ++s) {
     const bool update = active && s <= far;
     if (update) {
       double uxp = buf[16][kxp], vxp = buf[17][kxp], uxm = buf[16][kxm], vxm = buf[17][kxm];
@@ -226,6 +226,7 @@ __global__ __launch_bounds__(NODES, NODES <= 384 ? 3 : 2) void k_step_window(Fie
       moments_from_f(f, m);
       ir = recip(m[0]);
     }
+    if (s == nsteps) break;  // nothing is read from the window any more
     __syncthreads();  // every node of this step has been read
     if (update && !wall) put(f, m[1] * ir, m[2] * ir);
     if (WALLS && update && wall) {
@@ -241,17 +242,16 @@ __global__ __launch_bounds__(NODES, NODES <= 384 ? 3 : 2) void k_step_window(Fie
     }
     __syncthreads();
   }
-  if (LEVELS) {
-    if (!ok) flag[0] = 1;
-    return;
-  }
-  if (WALLS && wall) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) f[i] = buf[i][t];
-  }
   if (writes()) {
+    if (WALLS && wall) {
+      double fw[16];
+      neq_wall<VER>(cold->wall[wside], f, fw);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) F.fout[at + i * F.plane] = f[i];
+      for (int i = 0; i < 16; ++i) f[i] = fw[i];
+    }
+    double* out = F.fout + (LEVELS ? (nsteps - 1) * 16 * F.plane : 0) + at;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) out[i * F.plane] = f[i];
   }
   if (!ok) flag[0] = 1;
 }
