@@ -333,6 +333,39 @@ WinGeom default_window(const lbm_params* p) {
   return g;
 }
 
+// A call of few steps, or the last ones of a call. What a window's halo costs
+// in a launch does not shrink with its steps, so
+// - narrow grids with 12-step windows take those of columns / 8 steps for
+//   launches of no more (2000 x 16: 9.2 against 11.4 us for one step, 15.7
+//   against 17.8 for four);
+// - other grids take the one-step kernel for a single step where there are
+//   more than 128 windows (7.7 against 14.0 us at 512 x 128, 15.7 against
+//   31.6 at 768 x 256, 20.4 against 50.2 at 1024 x 256 with walls; 6.8
+//   against 6.6 at 128 x 64), and for two where the windows take three rounds
+//   or more (31.5 against 35.1 at 768 x 256; two rounds: 26.2 against 22.3 at
+//   400 x 300).
+WinPlan default_plan(const lbm_params* p) {
+  WinPlan w;
+  w.win = w.brief = default_window(p);
+  w.single = 0;
+  if (p->ny <= 16) {
+    const int wc = p->ny <= 8 ? 64 : 32;
+    make_window(p, wc, p->ny, wc / 8, &w.brief);
+    return w;
+  }
+  const long long windows = (long long)w.win.x.nwin * w.win.y.nwin;
+  if (windows > 128) w.single = 1;
+  if (window_rounds(w.win) >= 3) w.single = 2;
+  return w;
+}
+
+int next_launch(const WinPlan& w, int64_t left, const WinGeom** g) {
+  *g = nullptr;
+  if (left <= w.single) return 1;
+  *g = left <= w.brief.h ? &w.brief : &w.win;
+  return (int)std::min<int64_t>((*g)->h, left);
+}
+
 hipError_t launch_window(const Field& F, const Hot* c, const Cold* cold, int version, bool walls,
                          const WinGeom& g, int nsteps, int* flag, hipStream_t s) {
   // the smallest instance that holds the window (its LDS and registers decide
@@ -410,7 +443,7 @@ struct lbm_handle {
   int variant;
   TileShape tile;
   TileShape tile2;  // tile shape of variant 4 (two steps per launch)
-  WinGeom win;  // window shape of variant 3
+  WinPlan win;  // window shapes of variant 3
 };
 
 static Field field_of(const lbm_handle* h, int from) {
@@ -461,7 +494,7 @@ lbm_status lbm_create(const lbm_params* p, void* d_workspace, size_t ws_bytes, v
   h->dev = (Consts*)(base + 2 * 16 * h->plane * sizeof(double) + 256);
   h->cur = 0;
   h->variant = default_variant(p);
-  h->win = default_window(p);
+  h->win = default_plan(p);
   h->tile = default_tile(p->nx, p->ny);
   h->tile2 = default_tile2(p->nx, p->ny);
   e = hipMemsetAsync(h->flag, 0, 256, h->stream);
@@ -509,12 +542,16 @@ lbm_status lbm_step(lbm_handle* h, int64_t nsteps) {
     return LBM_OK;
   }
   if (h->variant == 3) {
-    // up to win.h steps per launch in LDS windows
-    const int64_t hmax = h->win.h;
-    for (int64_t n = 0; n < nsteps; n += hmax) {
-      const int k = (int)std::min<int64_t>(hmax, nsteps - n);
-      hipError_t e = launch_window(field_of(h, h->cur), &h->dev->hot, &h->dev->cold, h->p.eq_version,
-                                   has_walls(&h->p), h->win, k, h->flag, h->stream);
+    // several steps per launch in LDS windows
+    for (int64_t n = 0; n < nsteps;) {
+      const WinGeom* g;
+      const int k = next_launch(h->win, nsteps - n, &g);
+      n += k;
+      const Field F = field_of(h, h->cur);
+      hipError_t e = g ? launch_window(F, &h->dev->hot, &h->dev->cold, h->p.eq_version, has_walls(&h->p), *g, k,
+                                       h->flag, h->stream)
+                       : launch_step(F, &h->dev->hot, &h->dev->cold, h->p.eq_version, has_walls(&h->p), h->p.scheme,
+                                     0, h->tile, h->flag, h->stream);
       if (e != hipSuccess) return hip_fail(e, "windowed kernel launch");
       h->cur ^= 1;
     }
@@ -593,6 +630,7 @@ lbm_status lbm_set_variant(lbm_handle* h, int32_t variant) {
   if (variant == 3 && !window_problem(&h->p))
     return fail(LBM_EINVAL, "variant 3 needs scheme 0 and nx ny > %d nodes", SMALL_NODES);
   h->variant = variant;
+  h->win.single = 0;  // the chosen kernel takes every step
   return LBM_OK;
 }
 
@@ -631,15 +669,15 @@ lbm_status lbm_set_window(lbm_handle* h, int32_t cols, int32_t rows, int32_t ste
                 "window %d x %d with %d steps: need steps >= 1, a cut axis longer than 2 steps, "
                 "and at most %d nodes held",
                 cols, rows, steps, SMALL_NODES);
-  h->win = g;
+  h->win = WinPlan{g, g, 0};
   return LBM_OK;
 }
 
 lbm_status lbm_get_window(const lbm_handle* h, int32_t* cols, int32_t* rows, int32_t* steps) {
   if (!h) return fail(LBM_EINVAL, "handle is NULL");
-  if (cols) *cols = h->win.x.w;
-  if (rows) *rows = h->win.y.w;
-  if (steps) *steps = h->win.h;
+  if (cols) *cols = h->win.win.x.w;
+  if (rows) *rows = h->win.win.y.w;
+  if (steps) *steps = h->win.win.h;
   return LBM_OK;
 }
 
@@ -685,7 +723,7 @@ lbm_status lbm_tune(lbm_handle* h, int64_t probe_steps, double* d_scratch, size_
   const int wcand[] = {4, 2};
   TileShape best = h->tile;
   float best_t = 1e30f;
-  WinGeom best_win = h->win;
+  WinGeom best_win = h->win.win;
   float best_win_t = 1e30f;
   bool good = true;
   h->variant = 0;
@@ -763,7 +801,7 @@ lbm_status lbm_tune(lbm_handle* h, int64_t probe_steps, double* d_scratch, size_
     for (int i = 0; i < ns && good; ++i) {
       WinGeom g;
       if (!make_window(&h->p, shapes[i][0], shapes[i][1], shapes[i][2], &g)) continue;
-      h->win = g;
+      h->win = WinPlan{g, g, 0};
       float ms = 0;
       if (!(good = time_it(ms))) break;
       if (ms < best_win_t) {
@@ -771,7 +809,7 @@ lbm_status lbm_tune(lbm_handle* h, int64_t probe_steps, double* d_scratch, size_
         best_win = g;
       }
     }
-    h->win = best_win;
+    h->win = WinPlan{best_win, best_win, 0};
   }
   (void)hipEventDestroy(t0);
   (void)hipEventDestroy(t1);

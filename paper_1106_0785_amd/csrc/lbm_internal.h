@@ -49,6 +49,16 @@ bool small_problem(const lbm_params* p);
 bool window_problem(const lbm_params* p);
 bool narrow_problem(const lbm_params* p);
 WinGeom default_window(const lbm_params* p);
+// How a run of the windowed kernel is cut into launches.
+struct WinPlan {
+  WinGeom win;    // of up to win.h steps each
+  WinGeom brief;  // the window of a launch of at most brief.h steps
+  int single;     // a run's last steps, where they are no more than this, go one by one
+};
+WinPlan default_plan(const lbm_params* p);
+// The next launch of a run with `left` steps to go: its steps, and its window
+// or (NULL) the one-step kernel.
+int next_launch(const WinPlan& w, int64_t left, const WinGeom** g);
 WinAxis win_axis(int len, int w, int h, bool walls);
 hipError_t launch_small(const Field& F, const Hot* c, const Cold* cold, int version, bool walls, int nsteps,
                         int* flag, hipStream_t s);
