@@ -360,9 +360,13 @@ lbm_status lbm_adjoint_backward(lbm_adjoint* a, const double* d_rho0, const doub
   auto kwall = ver == 2 ? k_adj_walls<2> : ver == 3 ? k_adj_walls<3> : k_adj_walls<1>;
   const bool walls = has_walls(&a->p);
   // grids of more than 2048 blocks (8 per CU) take the two-blocks-per-CU form
+  // of the gather step (only where lbm_adjoint_set_variant asks for the gather
+  // step: by default they take the staged one): 90 against 114 us per step at
+  // 900 x 600; not version 3, which spills 94 registers there (203 against 154)
   const bool wide = (long long)L.gx * L.gy > 2048;
-  auto kstep = wide ? (ver == 2 ? k_adj_step<2, true> : ver == 3 ? k_adj_step<3, true> : k_adj_step<1, true>)
-                    : (ver == 2 ? k_adj_step<2, false> : ver == 3 ? k_adj_step<3, false> : k_adj_step<1, false>);
+  auto kstep = ver == 3 ? k_adj_step<3, false>
+               : wide   ? (ver == 2 ? k_adj_step<2, true> : k_adj_step<1, true>)
+                        : (ver == 2 ? k_adj_step<2, false> : k_adj_step<1, false>);
   auto kfused = ver == 2 ? k_adj_fused<2, 4> : ver == 3 ? k_adj_fused<3, 4> : k_adj_fused<1, 4>;
   const MarchGeom ag = adjoint_geom(a->p.nx, a->p.ny);
   const bool staged = a->variant == 0;
