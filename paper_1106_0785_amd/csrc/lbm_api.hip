@@ -428,6 +428,18 @@ TileShape default_tile(int nx, int ny) {
   return TileShape{best, WAVES, default_nt(nx, ny)};
 }
 
+// Tile heights that the tuner times, ascending: a fixed list and the one the
+// handle has, so that its choice is never slower than not tuning. Returns how
+// many (at most 17).
+int tile_heights(int start, int* out) {
+  const int fixed[] = {4, 8, 12, 16, 20, 24, 28, 32, 40, 48, 56, 64, 96, 128, 192, 256};
+  int n = 0;
+  for (int r : fixed) out[n++] = r;
+  if (std::find(out, out + n, start) == out + n) out[n++] = start;
+  std::sort(out, out + n);
+  return n;
+}
+
 }  // namespace lbm
 
 struct lbm_handle {
@@ -719,7 +731,8 @@ lbm_status lbm_tune(lbm_handle* h, int64_t probe_steps, double* d_scratch, size_
     ms *= (float)probe_steps / (float)n;  // per probe_steps steps
     return e == hipSuccess && st == LBM_OK;
   };
-  const int cand[] = {4, 8, 12, 16, 20, 24, 28, 32, 40, 48, 56, 64, 96, 128, 192, 256};
+  int cand[32];
+  const int ncand = tile_heights(h->tile.rows, cand);
   const int wcand[] = {4, 2};
   TileShape best = h->tile;
   float best_t = 1e30f;
@@ -731,7 +744,8 @@ lbm_status lbm_tune(lbm_handle* h, int64_t probe_steps, double* d_scratch, size_
     for (int wv : wcand) {
       if (wv != 4 && (has_walls(&h->p) || h->p.scheme == 1)) continue;
       int last_rows = -1;
-      for (int r : cand) {
+      for (int j = 0; j < ncand; ++j) {
+        const int r = cand[j];
         const MarchGeom g = march_geom(h->p.nx, h->p.ny, TileShape{r, wv, nt});
         if (g.rows == last_rows) continue;  // same tiling as a smaller candidate
         last_rows = g.rows;
@@ -751,13 +765,12 @@ lbm_status lbm_tune(lbm_handle* h, int64_t probe_steps, double* d_scratch, size_
   TileShape best2 = h->tile2;
   float best2_t = 1e30f;
   if (good && two_step) {
-    // two steps per launch: 2 or 4 waves, tile heights down from the
-    // fastest of the fused kernel's list, plus heights that give just under
+    // two steps per launch: 2 or 4 waves, the fused kernel's list of tile
+    // heights, plus heights that give just under
     // one, two or three tiles per workgroup slot (two per CU)
     h->variant = 4;
     int rc[32];
-    int nrc = 0;
-    for (int r : cand) rc[nrc++] = r;
+    int nrc = tile_heights(h->tile2.rows, rc);
     const long long strips = (h->p.nx + OSTRIP - 1) / OSTRIP;
     for (int k = 1; k <= 3; ++k) {
       const long long segs = std::max(1ll, (long long)k * 512 / strips);

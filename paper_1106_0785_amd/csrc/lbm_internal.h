@@ -36,6 +36,7 @@ bool has_walls(const lbm_params* p);
 hipError_t launch_step(const Field& F, const Hot* c, const Cold* cold, int version, bool walls, int scheme,
                        int variant, TileShape t, int* flag, hipStream_t s);
 TileShape default_tile(int nx, int ny);
+int tile_heights(int start, int* out);
 // Two steps per launch (lbm_fused2.h): scheme 0 without NEQ walls.
 bool two_step_problem(const lbm_params* p);
 March2Geom march2_geom(int nx, int ny, TileShape t);
