@@ -80,7 +80,7 @@ lbm_status lbm_batch_set_schedule(lbm_batch* b, int32_t region, int32_t steps_pe
 lbm_status lbm_batch_get_schedule(const lbm_batch* b, int32_t* region, int32_t* steps_per_launch, int32_t* nchunks);
 
 /* Launch form of the line instances: persistent = 1, one launch per equilibrium version for the
- * whole of an lbm_batch_step call (grid = min(chunks, workgroups resident on the device), chunks
+ * whole of an lbm_batch_step call of more than one block (grid = min(chunks, workgroups resident on the device), chunks
  * taken in ticket order, each waiting for its neighbours' previous block); 0, one launch per
  * block (the form at creation). Results are bitwise the same. timeout_ms in [0, 60000] bounds each
  * wait (wall clock; 0: the first dependency check of a call with two or more blocks raises the
