@@ -246,8 +246,12 @@ __global__ void k_persist_reset(unsigned long long* ctr, int* epoch, int n) {
 // check of a chunk's dependencies raises it, met or not, for tests);
 // the host reports the error and the state is then invalid.
 // status: health flag at word 0, error word at 16, ticket counter at 32.
+// Three waves per SIMD as k_batch_line, but for version 3 at region 128: at 168
+// registers it spills 44, and its short chunks feel that (300 uneven lines,
+// 200 steps, 12 per block: 3617 us, 3143 at two waves; region 256: 2757 and
+// 2813).
 template <int VER, int REGION>
-__global__ __launch_bounds__(REGION, 3) void k_batch_line_persistent(double* src, double* dst,
+__global__ __launch_bounds__(REGION, VER == 3 && REGION == 128 ? 2 : 3) void k_batch_line_persistent(double* src, double* dst,
                                                                const LineInst* __restrict__ insts,
                                                                const LineChunk* __restrict__ chunks, int nchunks,
                                                                const int* __restrict__ budget, int nsteps, int h,
