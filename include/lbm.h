@@ -146,10 +146,10 @@ lbm_status lbm_check(lbm_handle* h);
  *     default when ny <= 16 and up to 196608 nodes, 262144 with NEQ walls):
  *     workgroups hold overlapping windows of the grid
  *     in LDS (lbm_set_window) and take several steps per launch,
- *     recomputing the overlap; where it is the default (not chosen by
- *     lbm_set_variant, lbm_set_window or lbm_tune), a call's last one or two
- *     steps take variant 0 on grids where that is faster, and on narrow grids
- *     a few steps take windows of less overlap;
+ *     recomputing the overlap; where it is the default or lbm_tune's choice
+ *     (not lbm_set_variant's or lbm_set_window's), a call's last few steps
+ *     take variant 0 where that is faster, and by default on narrow grids
+ *     windows of less overlap;
  *   4 the fused kernel taking two time steps per launch (scheme 0 without
  *     NEQ walls, LBM_EINVAL otherwise; default above 196608 nodes): the intermediate level stays in LDS,
  *     so each node's distributions cross HBM once per two steps; an odd
