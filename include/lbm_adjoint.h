@@ -26,8 +26,8 @@ extern "C" {
 typedef struct lbm_adjoint lbm_adjoint;
 
 /* Device workspace for p, nsteps and a checkpoint interval (0 = round(sqrt(nsteps))):
- * checkpoints, segment store, two adjoint buffers, two per-node record buffers, the
- * s-gradient partials and constants; 0 if invalid (lbm_create's rules, or scheme 1). */
+ * checkpoints, segment store, two adjoint buffers, two per-node record buffers (used by
+ * kernel 1 of lbm_adjoint_set_variant only), the s-gradient partials and constants; 0 if invalid (lbm_create's rules, or scheme 1). */
 size_t lbm_adjoint_workspace_bytes(const lbm_params* p, int64_t nsteps, int32_t ckpt_interval);
 
 lbm_status lbm_adjoint_create(const lbm_params* p, int64_t nsteps, int32_t ckpt_interval, void* d_workspace,
@@ -52,12 +52,13 @@ lbm_status lbm_adjoint_backward(lbm_adjoint* a, const double* d_rho0, const doub
                                 const double* d_g_uy, const double* d_g_T, double* d_grad_rho0,
                                 double* d_grad_ux0, double* d_grad_uy0, double* d_grad_T0, double* d_grad_s);
 
-/* Kernel of the adjoint step: 0 the LDS-staged form (64-column tiles
- * marching up the grid, lambda^{n+1} and the records entering an LDS ring
- * once, ghost rules applied on entry; the default on large grids); 1 one
- * thread per node gathering its neighbours' lambda and records from global
- * memory (the default on small grids, where every tile would be a few rows
- * tall). Both give the same results to rounding. */
+/* Kernel of the adjoint step: 0 the LDS-staged form (62-column tiles
+ * marching up the grid, lambda^{n+1} and f^n entering an LDS ring once, the
+ * records formed and the ghost rules applied on entry); 1 one thread per node
+ * gathering its neighbours' lambda and records from global memory. Default: 1
+ * while its blocks of 64 x 4 nodes number at most 256, or at most 512 and the
+ * staged form's tiles would be taller than 4 rows; 0 above (from 400 x 200 or
+ * so up). Both give the same results to rounding. */
 lbm_status lbm_adjoint_set_variant(lbm_adjoint* a, int32_t variant);
 
 /* Synchronises the stream and reads the device health flag of every step

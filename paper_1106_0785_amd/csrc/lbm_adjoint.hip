@@ -194,7 +194,9 @@ static MarchGeom adjoint_geom(int nx, int ny) {
   return g;
 }
 
-// The gather step where its blocks have a CU each (13.8 us per step at
+// (Times per step of a backward pass over stored levels, launch gaps and
+// records passes included; the kernels alone take less, k_adj_step 12.2 us at
+// 512 x 128.) The gather step where its blocks have a CU each (13.8 us at
 // 512 x 128, the LDS-staged one 17.8), or two on half of them and the staged
 // step's tiles would be 8 rows tall (26.4 against 28.7 at 1000 x 128); the
 // staged step otherwise (18.1 against 21.9 at 400 x 200 with 4-row tiles, 27.4

